@@ -1,7 +1,8 @@
 // Bidirectional (non-causal) attention for gfx950, online softmax in fp32.
 //
 // Inputs: q [B, H, Ls, hd], k [B, Hkv, Ls, hd] (RoPE applied), vt [B, Hkv, hd, Ls]
-// (v transposed), rows >= L zero.  Output: o [B * L, H * hd] bf16.
+// (v transposed), rows >= L zero.  Output: o bf16 in K panels [H * hd / 32][B * L][32], the O
+// projection's A operand.
 // One workgroup = 64 queries of one head (4 wavefronts x 16 queries) times SPLIT parts of
 // the key range: with SPLIT = 2 a second group of 4 wavefronts runs the same queries over
 // the second half of the key tiles, and the partial softmax states (max, sum, O) are merged
@@ -274,13 +275,15 @@ __global__ __launch_bounds__(256 * SPLIT, SB && SPLIT == 1 ? 3 : 1) void k_atten
   const float inv = 1.0f / l;
   const int qi = q0 + r16;
   if (qi < L) {
-    uint16_t* dst = out + ((int64_t)b * L + qi) * ((int64_t)H * HD) + h * HD;
+    // K panels [H HD / 32][B L][32]: dimensions h HD + 16 d + 4 g .. + 3 of row b L + qi
+    const int64_t rows = (int64_t)gridDim.y / H * L;
+    uint16_t* dst = out + (h * (HD / 32) * rows + (int64_t)b * L + qi) * 32;
 #pragma unroll
     for (int d = 0; d < HD / 16; ++d) {
       u32x2_t p;
       p.x = pack_bf16x2(o[d][0] * inv, o[d][1] * inv);
       p.y = pack_bf16x2(o[d][2] * inv, o[d][3] * inv);
-      *reinterpret_cast<u32x2_t*>(dst + d * 16 + g * 4) = p;
+      *reinterpret_cast<u32x2_t*>(dst + (d >> 1) * rows * 32 + (d & 1) * 16 + g * 4) = p;
     }
   }
 }
@@ -509,13 +512,15 @@ __global__ __launch_bounds__(256 * SPLIT) __attribute__((amdgpu_waves_per_eu(4, 
   const float inv = 1.0f / l;
   const int qi = q0 + r16;
   if (qi < L) {
-    uint16_t* dst = out + ((int64_t)b * L + qi) * ((int64_t)H * HD) + h * HD;
+    // K panels [H HD / 32][B L][32]: dimensions h HD + 16 d + 4 g .. + 3 of row b L + qi
+    const int64_t rows = (int64_t)gridDim.y / H * L;
+    uint16_t* dst = out + (h * (HD / 32) * rows + (int64_t)b * L + qi) * 32;
 #pragma unroll
     for (int d = 0; d < HD / 16; ++d) {
       u32x2_t p;
       p.x = pack_bf16x2(o[d][0] * inv, o[d][1] * inv);
       p.y = pack_bf16x2(o[d][2] * inv, o[d][3] * inv);
-      *reinterpret_cast<u32x2_t*>(dst + d * 16 + g * 4) = p;
+      *reinterpret_cast<u32x2_t*>(dst + (d >> 1) * rows * 32 + (d & 1) * 16 + g * 4) = p;
     }
   }
 }

@@ -1,463 +1,354 @@
 // bf16 MFMA GEMM for gfx950: C[M, N] = A[M, K] . W[N, K]^T with fp32 accumulation.
 //
-// Both operands are K-contiguous (activations [M, K], weights [out, in]), so every
-// global load and every LDS fragment read is a 16-byte vector along K.  A workgroup
-// of WAVES_M x WAVES_N wavefronts owns a BM x BN tile; each wavefront owns
-// TM x TN blocks of 32 x 32 computed with v_mfma_f32_32x32x16_bf16.
+// A workgroup of WAVES_M x WAVES_N wavefronts owns a BM x BN tile; each wavefront owns
+// TM x TN blocks of 16 x 16 computed with v_mfma_f32_16x16x32_bf16.  The 16 x 16 shape is
+// chosen over 32 x 32 x 16 for power: large products run into the card's power limit, and a
+// register-only loop on random data sustains 1.99 PFLOP/s with it against 1.79.
 //
-// Pipelines (template parameter PIPE), all with two LDS buffers and one barrier per BK-slice:
-//   PIPE 0  slice kt+1 in registers while slice kt is multiplied out of LDS; fragments of
-//           k-step s+16 read during the MFMAs of step s (16-wave config: no registers
-//           left for a second stage).
-//   PIPE 1  slices kt+1 and kt+2 in registers, plain order (small-M config).
-//   PIPE 2  slices kt+1 and kt+2 in registers, and the slice loop body is branch-free so
-//           the scheduler can interleave everything: the LDS stash of slice kt+1 and the
-//           global fetch of slice kt+3 are spread over the MFMA steps of slice kt (MFMA /
-//           ds_read / ds_write / buffer_load groups), and the barrier sits before the last
-//           MFMA group, which then covers the first fragment reads of the next slice.
-//           Every thread stores all its chunks (rows past the tile land in spare LDS rows)
-//           and the fetch index is clamped, so nothing in the loop is conditional.  Memory
-//           and MFMA work overlap instead of alternating; on the 512 x 24576 x 4096
-//           gate/up GEMM this takes the 12-wave config from 113 to 90 us.
-// LDS rows are padded by 16 bytes so the lanes that read one fragment column hit distinct
-// banks.
+// Operands come in K panels of 32, so that every 1 KB load reads 1 KB of contiguous memory:
+//   A  [K / 32][M][32]: 16 rows of one panel are 1 KB
+//   W  (W_BLOCKS) 64 x 32 blocks, row-major inside, block (n / 64, k / 32) at
+//      ((n / 64) * K / 32 + k / 32) * 4 KB, N % 64 == 0; or (W_LM_HEAD) the LM head's packed
+//      layout (lm_head.hip), 1 KB blocks of 16 rows x 32 k, zero rows up to N's next multiple
+//      of 32.
+// What bounds the loop is the rate of cache lines that a CU's loads touch: with row-major
+// operands (64 bytes of each of 16 rows, twice the lines) the same loop runs 18 % slower at
+// 4096 x 37888 x 3584, and 25 % slower at 256 x 128 tiles.
+//
+// Pipeline: a ring of ST stages of one 32-wide K slice in LDS, filled by buffer loads that
+// write LDS directly (no staging registers, no LDS store instructions).  Section kt waits for
+// this wavefront's loads of slice kt + 1, passes one barrier, and then issues the MFMAs of
+// slice kt (fragments already in registers) with everything else spread between them: the
+// fragment reads of slice kt + 1 and the loads of slice kt + ST - 1, one per few MFMAs (loads
+// issued in a burst fill the address unit's queue and stall the MFMAs behind them).  An A
+// fragment is overwritten by the next slice's as soon as its row of MFMAs is issued; only the
+// B fragments have two register sets.  The loads of section kt go to the stage of slice
+// kt - 1, whose fragments every wavefront had in registers before this barrier, so the
+// barrier drains nothing but the loads it needs.
+// The 16-byte chunks of a 64-byte LDS row are XOR-permuted (on the global side of the load,
+// which can gather; the LDS side is linear): a 16-byte LDS read serves 16 lanes a cycle,
+// lanes {0-3, 12-15, 20-27} together, and the permutation puts their chunks on 16 distinct
+// 16-byte slots of the 256-byte bank window (counted conflicts: 0).
+//
+// Measured (back-to-back launches, weights from HBM, same box, against the register-staged
+// 32 x 32 x 16 loop with row-major A that this one replaced): gate/up + SwiGLU at
+// 4096 x 37888 x 3584 955 -> 789 us (1.41 PFLOP/s), 1280 x 24576 x 4096 229 -> 184 us
+// (1.40 PFLOP/s), 512 x 24576 x 4096 92.4 -> 83 us (1.24 PFLOP/s).
 //
 // Split-K (for outputs with too few tiles to fill the chip): split s of a tile
 // accumulates K-slices [s*nk, (s+1)*nk) and stores its fp32 partial tile (EPI_PART_F32);
 // a row-wise kernel downstream adds the partials in split order, so results do not depend
 // on scheduling, and applies what the output needs next (residual add + RMSNorm, or bias +
-// RoPE + head layout for q/k/v).
+// RoPE + head layout for q/k/v).  Every tile config sums K in the same order, so the split
+// count alone decides an output's bits.
 //
-// Epilogues:  EPI_BF16    C = bf16((acc + bias[n]) * scale)
+// The MFMA takes W as its first operand, so a lane holds one row of C and 4 consecutive
+// columns: epilogues store 8 or 16 bytes per lane straight from the accumulators, RoPE pairs
+// and gate/up pairs meet in one lane, and a row's statistics need two lane exchanges.
+// Epilogues:  EPI_BF16    C = bf16((acc + bias[n]) * scale), row-major
 //             EPI_ADD_F32 C(fp32) += acc            (residual stream update)
 //             EPI_PART_F32  split s stores acc to its own fp32 slab of C
-//             EPI_SWIGLU  weights interleave gate/up rows in groups of 32, so a
-//                         wavefront's two 32-column blocks hold gate and up of the
-//                         same outputs: C = bf16(silu(g) * u), ldc over ffn columns.
+//             EPI_SWIGLU  weights interleave gate/up rows in groups of 16:
+//                         C = bf16(silu(g) * u), stored as K panels [ffn / 32][M][32].
 //             EPI_QKV_ROPE  bias, rotate-half RoPE on q and k, head-major q/k and
 //                         transposed v written straight from the accumulators.
 //             EPI_TOP1    no C: per row and wavefront column range, (max, first arg max,
 //                         sum of exp) of the bf16 logits EPI_BF16 would store (Eq. 1).
-// Weights are either row-major or stored in 64 x 64 blocks (w_packed), in which case a
-// tile's BK-slice of W is a run of whole 8 KB blocks.
 // Requirements: K % (64 * splits) == 0; M, N arbitrary (tails clamped on load, masked
 // on store).
 #include <hip/hip_ext.h>
 #include <limits.h>
+
+#include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 #include "internal.hpp"
 
 namespace cora {
 
-constexpr int BK = 64;
-constexpr int LDK = BK + 8;  // padded LDS row, in bf16 elements
+constexpr int BK = 32;
+constexpr int GROUP_M = 8;  // M tiles walked before the next N tile (see tile_of)
 
-// N 16-byte loads at byte offsets voff + i * step (step uniform) through a buffer resource,
-// the last one from its own per-lane offset voff_last (an offset past the resource's range
-// makes the hardware return zeros without touching memory)
 template <int N>
-__device__ __forceinline__ void buf_load_tail(u32x4_t (&r)[N], __amdgpu_buffer_rsrc_t rs, int voff,
-                                              int voff_last, int step) {
-#pragma unroll
-  for (int i = 0; i < N; ++i)
-    r[i] = __builtin_bit_cast(
-        u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, i + 1 < N ? voff : voff_last, i * step, 0));
+__device__ __forceinline__ void wait_vm() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-// N 16-byte loads at per-chunk byte offsets voff[i] + koff (koff uniform); when the chunks
-// do not divide evenly and EXACT is false, the last one only where last_ok
-template <int N, bool EXACT>
-__device__ __forceinline__ void buf_load_chunks(u32x4_t (&r)[N], __amdgpu_buffer_rsrc_t rs,
-                                                const int (&voff)[N], int koff, bool last_ok) {
-#pragma unroll
-  for (int i = 0; i < N; ++i)
-    if (EXACT || i + 1 < N || last_ok)
-      r[i] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, voff[i] + koff, 0, 0));
+// 16 bytes per lane from buffer offset voff + soff straight into LDS: lane l's bytes land at
+// lds_off + 16 l.  Inline asm, because the compiler would wait for every such load before
+// the next LDS read; it has no register output.
+__device__ __forceinline__ void load_lds(uint32_t lds_off, int voff, u32x4_t rs, int soff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds_off),
+               "v"(voff), "s"(rs), "s"(soff)
+               : "memory");
 }
 
-// N 16-byte loads at byte offsets voff + i * step (step uniform); when the chunks do not
-// divide evenly and EXACT is false, the last one only where last_ok
-template <int N, bool EXACT>
-__device__ __forceinline__ void buf_load(u32x4_t (&r)[N], __amdgpu_buffer_rsrc_t rs, int voff,
-                                         int step, bool last_ok) {
-#pragma unroll
-  for (int i = 0; i < N; ++i)
-    if (EXACT || i + 1 < N || last_ok)
-      r[i] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, voff, i * step, 0));
+__device__ __forceinline__ u32x4_t buffer_rsrc(const void* p, int64_t bytes) {
+  const uint64_t a = (uint64_t)p;
+  return u32x4_t{(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu,
+                 (uint32_t)(bytes > 0xffffffffLL ? 0xffffffffLL : bytes), 0x00020000u};
 }
 
-template <int WAVES_M, int WAVES_N, int TM, int TN, int EPI, int PIPE>
-__global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm(GemmArgs g) {
-  constexpr int NT = WAVES_M * WAVES_N * 64;
-  constexpr int BM = WAVES_M * TM * 32, BN = WAVES_N * TN * 32;
-  constexpr int CA = (BM * BK / 8 + NT - 1) / NT;  // 16-byte chunks per thread per slice
-  constexpr int CB = (BN * BK / 8 + NT - 1) / NT;
-  constexpr bool A_EXACT = CA * NT * 8 == BM * BK, B_EXACT = CB * NT * 8 == BN * BK;
-  constexpr int NACC = TM * TN * 16;    // accumulators per thread
-  static_assert(NT % 8 == 0, "threads must cover whole 64-element rows");
-  static_assert(EPI != EPI_SWIGLU || TN % 2 == 0, "SwiGLU epilogue pairs 32-column blocks");
-  static_assert(PIPE != 2 || TM * TN == 4 || TM * TN == 2, "PIPE 2 schedules 4 or 2 MFMAs per k-step");
+// Tile of logical index t: N tiles in order, all M tiles (at most GROUP_M at a time) of one
+// before the next.  xcd_remap hands each XCD a contiguous run of that order, so the tiles an
+// XCD runs at once cover about as many M as N tiles and share both operands in its L2
+// (at 16 M tiles, 4096 x 37888 x 3584: 970 -> 949 us).
+__device__ __forceinline__ void tile_of(int t, int num_m, int n_tiles, int& tm, int& tn) {
+  if (num_m <= GROUP_M) {
+    tm = t % num_m;
+    tn = t / num_m;
+    return;
+  }
+  const int per = GROUP_M * (n_tiles / num_m), grp = t / per, first = grp * GROUP_M;
+  const int gm = min(GROUP_M, num_m - first), r = t - grp * per;
+  tm = first + r % gm;
+  tn = r / gm;
+}
 
-  // PIPE 2 stores every thread's chunks unconditionally: rows past the tile land in spare
-  // LDS rows (CA * NT / 8 >= BM)
-  constexpr int A_ROWS = PIPE == 2 ? CA * NT / 8 : BM, B_ROWS = PIPE == 2 ? CB * NT / 8 : BN;
-  // one LDS array: the operand buffers As [2][A_ROWS * LDK] then Bs [2][B_ROWS * LDK]; the
-  // epilogues reuse it whole
-  __shared__ __attribute__((aligned(16))) uint16_t lds[2 * (A_ROWS + B_ROWS) * LDK];
-  auto As = reinterpret_cast<uint16_t(*)[A_ROWS * LDK]>(lds);
-  auto Bs = reinterpret_cast<uint16_t(*)[B_ROWS * LDK]>(lds + 2 * A_ROWS * LDK);
+template <int WAVES_M, int WAVES_N, int TM, int TN, int ST, int OCC, int EPI>
+__global__ __launch_bounds__(WAVES_M* WAVES_N * 64, OCC) void k_gemm(GemmArgs g) {
+  constexpr int NW = WAVES_M * WAVES_N;
+  constexpr int WR = TM * 16, WC = TN * 16;  // wavefront tile
+  constexpr int BM = WAVES_M * WR, BN = WAVES_N * WC;
+  constexpr int GA = BM / 16, GB = BN / 16;  // 1 KB loads (16 rows of 64 bytes) per slice
+  // loads per wavefront and slice; where they do not divide evenly some load twice the same
+  // 1 KB to the same place, so that every wavefront counts alike
+  constexpr int LA = (GA + NW - 1) / NW, LB = (GB + NW - 1) / NW, LPW = LA + LB;
+  constexpr int ROWB = BK * 2, STAGE = (BM + BN) * ROWB;
+  static_assert(ST % 2 == 1 && ST >= 3 && ST <= 9, "the tail pairs sections: an odd number of stages");
+  static_assert(EPI != EPI_SWIGLU || TN % 2 == 0, "SwiGLU epilogue pairs 16-column blocks");
+  __shared__ __attribute__((aligned(1024))) uint16_t lds[ST * STAGE / 2];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-  const int num_m = (g.M + BM - 1) / BM;
-  // logical order: split-major, then N tile, then M tile.  xcd_remap hands each XCD a
-  // contiguous run of that order, so an XCD's workgroups share one K range (its L2 holds
-  // only that range of A) and, within it, the M tiles of a run of N tiles (each weight
-  // byte is fetched by one XCD).
+  // logical order: split-major, then tile_of.  An XCD's workgroups share one K range (its L2
+  // holds only that range of A).
   const int li = xcd_remap(blockIdx.x, gridDim.x);
   const int n_tiles = gridDim.x / g.splits;
-  const int split = li / n_tiles, tile = li - split * n_tiles;
-  const int tile_m = tile % num_m, tile_n = tile / num_m;
+  const int split = li / n_tiles;
+  int tile_m, tile_n;
+  tile_of(li - split * n_tiles, (g.M + BM - 1) / BM, n_tiles, tile_m, tile_n);
   const int m0 = tile_m * BM, n0 = tile_n * BN;
-  const int nk = g.K / BK / g.splits;
-  const int64_t k_base = (int64_t)split * nk * BK;
+  const int nk = g.K / BK / g.splits;  // even: K % (64 * splits) == 0
+  const int kt0 = split * nk;
 
-  // operands through buffer resources: 32-bit byte offsets, and rows past M or N read
-  // as zero (hardware range check), so tails need no clamping
-  const int64_t a_bytes = (int64_t)g.M * g.lda * 2, b_bytes = (int64_t)g.N * g.ldw * 2;
-  const __amdgpu_buffer_rsrc_t a_rs = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)g.A, (short)0, (int)(a_bytes > 0xffffffffLL ? 0xffffffffu : (uint32_t)a_bytes),
-      0x00020000);
-  const __amdgpu_buffer_rsrc_t b_rs = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)g.W, (short)0, (int)(b_bytes > 0xffffffffLL ? 0xffffffffu : (uint32_t)b_bytes),
-      0x00020000);
-  const int c_r = tid >> 3, c_k = (tid & 7) * 8;
-  const int a_off = (int)(((int64_t)(m0 + c_r) * g.lda + k_base + c_k) * 2);
-  const int b_off = (int)(((int64_t)(n0 + c_r) * g.ldw + k_base + c_k) * 2);  // row-major
-  const int a_step = (NT / 8) * (int)g.lda * 2;  // next chunk of this thread: NT/8 rows down
-  const int b_step = (NT / 8) * (int)g.ldw * 2;
-  const int lds_off = c_r * LDK + c_k;
-  constexpr int LDS_STEP = (NT / 8) * LDK;
-  const bool a_last = tid + (CA - 1) * NT < BM * BK / 8;
-  const bool b_last = tid + (CB - 1) * NT < BN * BK / 8;
-  // B chunk i of slice kt sits at byte b_chunk[i] + kt * b_kstride: row-major weights (row
-  // c_r + i NT / 8 of the tile, next slice 128 bytes on) or weights packed in 64 x 64 blocks
-  // (row-major inside, block (row / 64, k / 64) at (row / 64 * K / 64 + k / 64) * 8 KB, next
-  // slice 8 KB on: a tile slice reads whole 8 KB blocks).  A chunk past the tile or past N
-  // reads from the first byte past the operand: zeros, no memory traffic.
-  const int b_oob = (int)(b_bytes > 0x7fffffffLL ? 0x7fffffff : b_bytes);
-  const int b_kstride = g.w_packed ? 64 * BK * 2 : BK * 2;
-  int b_chunk[CB];
+  // W is addressed from this tile's first row group (64-bit base, 32-bit offsets inside);
+  // rows past M or N are clamped to the last one, so no load leaves the operands
+  const bool lm = g.w_layout == W_LM_HEAD;
+  const int n_rows = lm ? (g.N + 31) / 32 * 32 : g.N;
+  const int64_t w_base = (int64_t)(n0 >> 6) * 64 * g.K * 2;
+  const u32x4_t a_rs = buffer_rsrc(g.A, (int64_t)g.M * g.K * 2);
+  const u32x4_t b_rs = buffer_rsrc(reinterpret_cast<const char*>(g.W) + w_base, (int64_t)n_rows * g.K * 2 - w_base);
+  const int lr = lane >> 2, ls = lane & 3;  // this lane's row and 16-byte slot of a load
+  auto swz = [](int r) {                    // 0, 2, 3, 1 for r / 4 = 0 .. 3
+    const int k = (r >> 2) & 3;
+    return (k >> 1) | (((k ^ (k >> 1)) & 1) << 1);
+  };
+  int voa[LA], vob[LB];
 #pragma unroll
-  for (int i = 0; i < CB; ++i) {
-    const int j = tid + i * NT, row = j >> 3;
-    const bool in = j < BN * BK / 8 && n0 + row < g.N;
-    if (!g.w_packed)
-      b_chunk[i] = in ? b_off + i * b_step : b_oob;
-    else
-      b_chunk[i] = in ? (int)((((int64_t)((n0 + row) >> 6) * (g.K / 64) + k_base / 64) * 4096 +
-                               (row & 63) * 64 + (j & 7) * 8) * 2)
-                      : b_oob;
+  for (int t = 0; t < LA; ++t) {
+    const int r = (t * NW + wave) % GA * 16 + lr;
+    voa[t] = min(m0 + r, g.M - 1) * 64 + (ls ^ swz(lr)) * 16;
   }
+#pragma unroll
+  for (int t = 0; t < LB; ++t) {
+    const int n = min(n0 + (t * NW + wave) % GB * 16 + lr, n_rows - 1) - (n0 & ~63), c = ls ^ swz(lr);
+    vob[t] = lm ? (n >> 5) * 64 * g.K + ((n >> 4) & 1) * 2048 + ((n & 15) + 16 * c) * 16
+                : (n >> 6) * 128 * g.K + (n & 63) * 64 + c * 16;
+  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+  // load t of this wavefront's share of slice kt, into the stage at byte offset st
+  auto issue = [&](int kt, uint32_t st, int t) {
+    const int k = kt0 + kt;
+    if (t < LA)
+      load_lds(lds0 + st + (GA % NW ? (t * NW + wave) % GA : t * NW + wave) * 1024, voa[t < LA ? t : 0], a_rs,
+               k * g.M * 64);
+    else
+      load_lds(lds0 + st + BM * ROWB + (GB % NW ? ((t - LA) * NW + wave) % GB : (t - LA) * NW + wave) * 1024,
+               vob[t >= LA ? t - LA : 0], b_rs, lm ? (k >> 1) * 4096 + (k & 1) * 1024 : k * 4096);
+  };
 
-  f32x16_t acc[TM][TN];
+  f32x4_t acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  u32x4_t ra0[CA], rb0[CB];
-  [[maybe_unused]] u32x4_t ra1[CA], rb1[CB];
-#define GEMM_FETCH(ra, rb, kt)                                            \
-  do {                                                                    \
-    buf_load<CA, A_EXACT>(ra, a_rs, a_off + (kt) * BK * 2, a_step, a_last); \
-    buf_load_chunks<CB, B_EXACT>(rb, b_rs, b_chunk, (kt) * b_kstride, b_last); \
-  } while (0)
-  auto stash = [&](int buf, const u32x4_t(&ra)[CA], const u32x4_t(&rb)[CB]) {
+  // fragments: lane holds row (lane % 16), k chunk (lane / 16) * 8
+  const int fr = lane & 15, fc = lane >> 4;
+  const int slot = (fc ^ swz(fr)) * 16;
+  const int ka = (wm * WR + fr) * ROWB + slot, kb = BM * ROWB + (wn * WC + fr) * ROWB + slot;
+  const char* lp = reinterpret_cast<const char*>(lds);
+  auto frag = [&](int off) { return as_bf16x8(*reinterpret_cast<const u32x4_t*>(lp + off)); };
+  constexpr int NM = TM * TN;
+  bf16x8_t fa[TM], fb0[TN], fb1[TN];
+  auto section = [&](auto load_c, auto read_c, int st_next, int kt_load, uint32_t st_load,
+                     const bf16x8_t(&fb)[TN], bf16x8_t(&nb)[TN]) {
+    constexpr bool LOAD = decltype(load_c)::value, READ = decltype(read_c)::value;
 #pragma unroll
-    for (int i = 0; i < CA; ++i)
-      if (A_EXACT || i + 1 < CA || a_last)
-        *reinterpret_cast<u32x4_t*>(&As[buf][lds_off + i * LDS_STEP]) = ra[i];
+    for (int q = 0; q < NM; ++q) {
+      const int i = q / TN, j = q % TN;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
+      if constexpr (READ) {
+        if (i == 0) nb[j] = frag(st_next + kb + j * 16 * ROWB);
+        if (j == TN - 1) fa[i] = frag(st_next + ka + i * 16 * ROWB);
+      }
+      if constexpr (LOAD) {
 #pragma unroll
-    for (int i = 0; i < CB; ++i)
-      if (B_EXACT || i + 1 < CB || b_last)
-        *reinterpret_cast<u32x4_t*>(&Bs[buf][lds_off + i * LDS_STEP]) = rb[i];
-  };
-
-  // fragment read offsets: lane holds row (lane % 32), k half (lane / 32) * 8
-  const int frag_r = lane & 31, frag_k = (lane >> 5) * 8;
-  const int a_base = (wm * TM * 32 + frag_r) * LDK + frag_k;
-  const int b_base = (wn * TN * 32 + frag_r) * LDK + frag_k;
-  // fragments of step kk+16 are read while the MFMAs of step kk run; scheduling
-  // barriers keep the compiler from hoisting a whole slice's reads (register pressure)
-  auto load_frags = [&](int buf, int kk, bf16x8_t(&fa)[TM], bf16x8_t(&fb)[TN]) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-      fa[i] = as_bf16x8(*reinterpret_cast<const u32x4_t*>(&As[buf][a_base + i * 32 * LDK + kk]));
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-      fb[j] = as_bf16x8(*reinterpret_cast<const u32x4_t*>(&Bs[buf][b_base + j * 32 * LDK + kk]));
-  };
-  auto mfmas = [&](const bf16x8_t(&fa)[TM], const bf16x8_t(&fb)[TN]) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
-  };
-  auto compute = [&](int buf) {
-    bf16x8_t fa0[TM], fb0[TN], fa1[TM], fb1[TN];
-    load_frags(buf, 0, fa0, fb0);
-    load_frags(buf, 16, fa1, fb1);
-    mfmas(fa0, fb0);
-    __builtin_amdgcn_sched_barrier(0);
-    load_frags(buf, 32, fa0, fb0);
-    mfmas(fa1, fb1);
-    __builtin_amdgcn_sched_barrier(0);
-    load_frags(buf, 48, fa1, fb1);
-    mfmas(fa0, fb0);
-    __builtin_amdgcn_sched_barrier(0);
-    mfmas(fa1, fb1);
-  };
-
-  if constexpr (PIPE == 2) {
-    bf16x8_t fa0[TM], fb0[TN], fa1[TM], fb1[TN];
-    auto stash_a = [&](int buf, const u32x4_t(&ra)[CA]) {
-#pragma unroll
-      for (int i = 0; i < CA; ++i)
-        *reinterpret_cast<u32x4_t*>(&As[buf][lds_off + i * LDS_STEP]) = ra[i];
-    };
-    auto stash_b = [&](int buf, const u32x4_t(&rb)[CB]) {
-#pragma unroll
-      for (int i = 0; i < CB; ++i)
-        *reinterpret_cast<u32x4_t*>(&Bs[buf][lds_off + i * LDS_STEP]) = rb[i];
-    };
-    // all chunks of every thread: rows past the tile read real rows or the range-checked
-    // zeros past M / N, and are stored to the spare LDS rows
-    // a thread's chunk past the tile (CA * NT / 8 > BM) reads from the first byte past the
-    // operand: zeros, no memory traffic
-    const int a_tail = A_EXACT || a_last ? a_off : (int)(a_bytes > 0x7fffffffLL ? 0x7fffffff : a_bytes);
-#define FETCH_ALL(ra, rb, kt)                                                              \
-  do {                                                                                     \
-    buf_load_tail<CA>(ra, a_rs, a_off + (kt) * BK * 2, a_tail + (kt) * BK * 2, a_step);    \
-    buf_load_chunks<CB, true>(rb, b_rs, b_chunk, (kt) * b_kstride, true);                 \
-  } while (0)
-#define SG(mask, n) __builtin_amdgcn_sched_group_barrier(mask, n, 0)
-    // slice KT out of LDS buffer KT & 1; RAN/RBN hold slice KT+1 on entry and receive
-    // slice KT+3 (clamped to the last slice)
-#define SLICE(KT, RAN, RBN)                                                             \
-  do {                                                                                  \
-    const int kt_ = (KT), cur = kt_ & 1;                                                \
-    load_frags(cur, 16, fa1, fb1);                                                      \
-    mfmas(fa0, fb0);                                                                    \
-    stash_a(cur ^ 1, RAN);                                                              \
-    _Pragma("unroll") for (int q = 0; q < TM * TN; ++q) { SG(0x008, 1); SG(0x100, 1); SG(0x200, 1); } \
-    __builtin_amdgcn_sched_barrier(0);                                                  \
-    load_frags(cur, 32, fa0, fb0);                                                      \
-    mfmas(fa1, fb1);                                                                    \
-    stash_b(cur ^ 1, RBN);                                                              \
-    _Pragma("unroll") for (int q = 0; q < TM * TN; ++q) { SG(0x008, 1); SG(0x100, 1); SG(0x200, 1); } \
-    __builtin_amdgcn_sched_barrier(0);                                                  \
-    load_frags(cur, 48, fa1, fb1);                                                      \
-    mfmas(fa0, fb0);                                                                    \
-    FETCH_ALL(RAN, RBN, kt_ + 3 < nk ? kt_ + 3 : nk - 1);                               \
-    _Pragma("unroll") for (int q = 0; q < TM * TN; ++q) { SG(0x008, 1); SG(0x100, 1); SG(0x020, 2); } \
-    __builtin_amdgcn_sched_barrier(0);                                                  \
-    __syncthreads();                                                                    \
-    load_frags(cur ^ 1, 0, fa0, fb0);                                                   \
-    mfmas(fa1, fb1);                                                                    \
-    _Pragma("unroll") for (int q = 0; q < TM * TN; ++q) { SG(0x008, 1); SG(0x100, 1); }       \
-    __builtin_amdgcn_sched_barrier(0);                                                  \
-  } while (0)
-    FETCH_ALL(ra0, rb0, 0);
-    FETCH_ALL(ra1, rb1, nk > 1 ? 1 : 0);
-    stash_a(0, ra0);
-    stash_b(0, rb0);
-    FETCH_ALL(ra0, rb0, nk > 2 ? 2 : nk - 1);
-    __syncthreads();
-    load_frags(0, 0, fa0, fb0);
-    int kt = 0;
-    for (; kt + 1 < nk; kt += 2) {
-      SLICE(kt, ra1, rb1);
-      SLICE(kt + 1, ra0, rb0);
+        for (int t = 0; t < LPW; ++t)
+          if (t * NM / LPW + (NM > LPW ? 1 : 0) == q) issue(kt_load, st_load, t);
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
-    if (kt < nk) SLICE(kt, ra1, rb1);
-#undef SLICE
-#undef SG
-#undef FETCH_ALL
-  } else if constexpr (PIPE == 1) {
-    // slices kt (LDS), kt+1 and kt+2 (registers) in flight
-    GEMM_FETCH(ra0, rb0, 0);
-    if (nk > 1) GEMM_FETCH(ra1, rb1, 1);
-    stash(0, ra0, rb0);
-    __syncthreads();
-    int kt = 0;
-    for (; kt + 1 < nk; kt += 2) {
-      if (kt + 2 < nk) GEMM_FETCH(ra0, rb0, kt + 2);
-      compute(0);
-      stash(1, ra1, rb1);
-      __syncthreads();
-      if (kt + 3 < nk) GEMM_FETCH(ra1, rb1, kt + 3);
-      compute(1);
-      if (kt + 2 < nk) stash(0, ra0, rb0);
-      __syncthreads();
-    }
-    if (kt < nk) compute(0);  // odd slice count: the last slice sits in buffer 0
-  } else {
-    // slice kt in LDS, slice kt+1 in registers
-    GEMM_FETCH(ra0, rb0, 0);
-    stash(0, ra0, rb0);
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-      if (kt + 1 < nk) GEMM_FETCH(ra0, rb0, kt + 1);
-      compute(kt & 1);
-      if (kt + 1 < nk) stash((kt + 1) & 1, ra0, rb0);
-      __syncthreads();
-    }
+  };
+  // prologue: slices 0 .. ST - 2 in flight (past the last one: it again, never read)
+#pragma unroll
+  for (int u = 0; u < ST - 1; ++u)
+#pragma unroll
+    for (int t = 0; t < LPW; ++t) issue(u < nk ? u : nk - 1, u * STAGE, t);
+  wait_vm<(ST - 2) * LPW>();
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < TN; ++j) fb0[j] = frag(kb + j * 16 * ROWB);
+#pragma unroll
+  for (int i = 0; i < TM; ++i) fa[i] = frag(ka + i * 16 * ROWB);
+  __builtin_amdgcn_sched_barrier(0);
+  int rd = 0, wr = (ST - 1) * STAGE;  // stage of slice kt, and of slices kt - 1 and kt + ST - 1
+  // section KT; NEWER: slices after KT + 1 whose loads may still be in flight at the barrier
+#define SECTION(LOAD, READ, NEWER, KT, FB, NB)                                              \
+  do {                                                                                      \
+    const int nx = rd + STAGE == ST * STAGE ? 0 : rd + STAGE;                               \
+    if constexpr (READ) {                                                                   \
+      wait_vm<((NEWER) > 0 ? (NEWER) : 0) * LPW>();                                         \
+      asm volatile("s_barrier" ::: "memory");                                               \
+    }                                                                                       \
+    section(std::bool_constant<(LOAD)>{}, std::bool_constant<(READ)>{}, nx, (KT) + ST - 1, (uint32_t)wr, FB, NB); \
+    wr = rd;                                                                                \
+    rd = nx;                                                                                \
+  } while (0)
+  // nk and ST - 1 are even, so the sections that load come in pairs too
+  for (int kt = 0; kt + ST - 1 < nk; kt += 2) {
+    SECTION(true, true, ST - 3, kt, fb0, fb1);
+    SECTION(true, true, ST - 3, kt + 1, fb1, fb0);
   }
-#undef GEMM_FETCH
+  // the last ST - 1 slices (or all nk of them): nothing left to load
+#define TAIL(P)                                     \
+  if constexpr (2 * (P) <= ST - 1) {                \
+    if (nk >= 2 * (P)) {                            \
+      SECTION(false, true, 2 * (P)-2, 0, fb0, fb1); \
+      SECTION(false, (P) > 1, 2 * (P)-3, 0, fb1, fb0); \
+    }                                               \
+  }
+  TAIL(4) TAIL(3) TAIL(2) TAIL(1)
+#undef TAIL
+#undef SECTION
+  wait_vm<0>();
+
   // epilogue: acc[i][j][e] is C[row, col] with
-  //   row = m0 + wm*TM*32 + i*32 + 8*(e/4) + 4*(lane/32) + e%4,  col = n0 + wn*TN*32 + j*32 + lane%32
-  const int col_l = lane & 31, row_q = (lane >> 5) * 4;
-  // The SwiGLU, QKV and fp32 epilogues stage each wavefront's finished tile in LDS (the
-  // operand buffers are free once every wavefront is past its last slice) and write it back
-  // as 16-byte stores: 128 contiguous bytes per row of q, k and the SwiGLU output, per head
-  // dimension of the transposed v and per 32 floats of an fp32 row, instead of 2- or 4-byte
-  // stores spread over 32 rows.
-  constexpr int WR = TM * 32, WC = TN * 32;  // wavefront tile
+  //   row = m0 + wm WR + 16 i + lane % 16,  col = n0 + wn WC + 16 j + 4 (lane / 16) + e
+  const int row0 = m0 + wm * WR + fr, col0 = n0 + wn * WC + 4 * fc;
   if constexpr (EPI == EPI_SWIGLU) {
-    constexpr int OC = WC / 2;                // output columns of the tile (gate/up pairs)
-    constexpr int SPS = OC + 8;               // staged row pitch, bf16
-    static_assert(sizeof(lds) >= (size_t)WAVES_M * WAVES_N * WR * SPS * 2, "stage");
-    __syncthreads();                          // every wavefront is done with As / Bs
-    uint16_t* scr = lds + wave * WR * SPS;
+    // lanes of 16 rows x 16 outputs write 32 bytes of each of 16 consecutive 64-byte rows
+    uint16_t* C = reinterpret_cast<uint16_t*>(g.C);
 #pragma unroll
-    for (int t = 0; t < TN / 2; ++t)
+    for (int i = 0; i < TM; ++i) {
+      const int row = row0 + i * 16;
+      if (row >= g.M) continue;
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int t = 0; t < TN / 2; ++t) {
+        float o[4];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
+        for (int e = 0; e < 4; ++e) {
           const float gt = acc[i][2 * t][e], up = acc[i][2 * t + 1][e];
           const float sg = gt / (1.0f + __expf(-gt));
-          scr[(i * 32 + 8 * (e >> 2) + row_q + (e & 3)) * SPS + t * 32 + col_l] =
-              (uint16_t)f32_to_bf16_bits(sg * up);
+          o[e] = sg * up;
         }
-    __syncthreads();
-    uint16_t* C = reinterpret_cast<uint16_t*>(g.C);
-    const int pcol0 = n0 + wn * WC;           // first physical column of the wavefront
-    const int jcol0 = pcol0 / 2;              // its first output (ffn) column
-    const int ncol = min(OC, (g.N - pcol0) / 2);
-    constexpr int CPR = OC / 8;               // 16-byte chunks per staged row
-    const int64_t row0 = m0 + wm * WR;
-    if (ncol > 0) {
-#pragma unroll
-      for (int k = 0; k < WR * CPR / 64; ++k) {
-        const int id = lane + 64 * k, r = id / CPR, cc = (id % CPR) * 8;
-        if (row0 + r < g.M && cc < ncol)
-          *reinterpret_cast<u32x4_t*>(C + (row0 + r) * g.ldc + jcol0 + cc) =
-              *reinterpret_cast<const u32x4_t*>(scr + r * SPS + cc);
+        const int col = (n0 + wn * WC) / 2 + t * 16 + 4 * fc;
+        if (col < g.N / 2)
+          *reinterpret_cast<u32x2_t*>(C + ((int64_t)(col >> 5) * g.M + row) * 32 + (col & 31)) =
+              u32x2_t{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
       }
     }
   } else if constexpr (EPI == EPI_QKV_ROPE) {
-    // q/k columns are pair-interleaved within a head, so the rotate-half partner of
-    // column c is column c ^ 1, held by lane ^ 1 for the same rows.  A wavefront's WC
-    // columns lie in one head of one section (q, k or v): section widths are multiples of
-    // 64.  q and k are staged row-major and leave as rows of the head layout; v is staged
-    // transposed and leaves as runs of 8 positions of the transposed layout.
+    // q/k columns are pair-interleaved within a head, so the rotate-half partner of an even
+    // column is the next one, in the same lane.  A 16-column block lies in one head of one
+    // section (q, k or v): section widths are multiples of 64.  v leaves transposed: the
+    // block passes through this wavefront's part of LDS (free once every wavefront is past
+    // its last slice) and is written as runs of 8 positions.
     const QkvOut& o = g.qkv;
     const int hd = o.head_dim, half = hd / 2;
     const int hq = o.n_heads * hd, hkv = o.n_kv_heads * hd;
-    const int c0 = n0 + wn * WC;
-    const int sec = c0 < hq ? 0 : (c0 < hq + hkv ? 1 : 2);
-    const int cc0 = c0 - (sec == 0 ? 0 : (sec == 1 ? hq : hq + hkv));
-    const int head = cc0 / hd, pd0 = cc0 % hd;
-    constexpr int SPS = WC + 8, SPV = WR + 8;  // staged pitches, bf16
-    static_assert(sizeof(lds) >= (size_t)WAVES_M * WAVES_N * WR * SPS * 2 &&
-                  sizeof(lds) >= (size_t)WAVES_M * WAVES_N * WC * SPV * 2, "stage");
-    __syncthreads();                           // every wavefront is done with As / Bs
-    uint16_t* scr = lds + wave * (WR * SPS > WC * SPV ? WR * SPS : WC * SPV);
-    const int64_t row0 = m0 + wm * WR;
+    constexpr int SPV = WR + 8;  // staged pitch, bf16
+    constexpr int CPC = WR / 8;  // runs of 8 positions per head dimension
+    constexpr int NCH = (16 * CPC + 63) / 64;
+    static_assert(sizeof(lds) >= (size_t)NW * 16 * SPV * 2, "stage");
+    __syncthreads();
+    uint16_t* scr = lds + wave * 16 * SPV;
+    // batch row and position of this lane's rows and of its runs: divided out once, not per
+    // block column
+    int rb[TM], rp[TM], vb[NCH], vp[NCH];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const int m = min(row0 + i * 16, g.M - 1);
+      rb[i] = m / o.L;
+      rp[i] = m - rb[i] * o.L;
+    }
+#pragma unroll
+    for (int k = 0; k < NCH; ++k) {
+      const int m = m0 + wm * WR + (lane + 64 * k) % CPC * 8;
+      vb[k] = m / o.L;
+      vp[k] = m - vb[k] * o.L;
+    }
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-      const int col = c0 + j * 32 + col_l;
-      const float bias = (col < g.N && g.bias) ? g.bias[col] : 0.f;
-      const int ii = (pd0 + j * 32 + col_l) >> 1;
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int hf = 0; hf < 2; ++hf) {  // rows 8 e4 + .. of e4 = 2 hf, 2 hf + 1
-          float x[2][4], partner[2][4];
-#pragma unroll
-          for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-              x[u][t] = acc[i][j][(2 * hf + u) * 4 + t] + bias;
-              partner[u][t] = __shfl_xor(x[u][t], 1, 64);
-            }
-#pragma unroll
-          for (int u = 0; u < 2; ++u) {
-            const int rl = i * 32 + row_q + 16 * hf + 8 * u;  // staged row of element t = 0
-            if (sec < 2) {
-              // the cos/sin loads of these 4 elements are issued before the LDS writes
-              float cs[4], sn[4];
-              int pos = (int)((row0 + rl) % o.L);
-#pragma unroll
-              for (int t = 0; t < 4; ++t) {
-                cs[t] = o.cos_t[pos * half + ii];
-                sn[t] = o.sin_t[pos * half + ii];
-                if (++pos == o.L) pos = 0;
-              }
-#pragma unroll
-              for (int t = 0; t < 4; ++t) {
-                const float r = (col_l & 1) ? x[u][t] * cs[t] + partner[u][t] * sn[t]
-                                            : x[u][t] * cs[t] - partner[u][t] * sn[t];
-                scr[(rl + t) * SPS + j * 32 + col_l] = (uint16_t)f32_to_bf16_bits(r);
-              }
-            } else {
-              u32x2_t v2;
-              v2.x = pack_bf16x2(x[u][0], x[u][1]);
-              v2.y = pack_bf16x2(x[u][2], x[u][3]);
-              *reinterpret_cast<u32x2_t*>(scr + (j * 32 + col_l) * SPV + rl) = v2;
-            }
-          }
-        }
-    }
-    __syncthreads();
-    if (c0 < g.N) {
+      const int c0 = n0 + wn * WC + j * 16;  // wave-uniform
+      if (c0 >= g.N) continue;
+      const int sec = c0 < hq ? 0 : (c0 < hq + hkv ? 1 : 2);
+      const int cc0 = c0 - (sec == 0 ? 0 : (sec == 1 ? hq : hq + hkv));
+      const int head = cc0 / hd, d0 = cc0 % hd;
+      const float4 bias = g.bias ? *reinterpret_cast<const float4*>(g.bias + c0 + 4 * fc) : float4{0.f, 0.f, 0.f, 0.f};
       if (sec < 2) {
-        constexpr int CPR = WC / 8;            // 16-byte chunks per staged row
         uint16_t* base = sec == 0 ? o.q : o.k;
-        const int nh = sec == 0 ? o.n_heads : o.n_kv_heads;
+        const int nh = sec == 0 ? o.n_heads : o.n_kv_heads, pd = d0 + 4 * fc;
+        // the cos/sin loads of a block column are issued before its first store (a load
+        // queued behind a store waits for it too)
+        float2 cs[TM], sn[TM];
 #pragma unroll
-        for (int k = 0; k < WR * CPR / 64; ++k) {
-          const int id = lane + 64 * k, r = id / CPR, cc = (id % CPR) * 8;
-          const int64_t m = row0 + r;
-          if (m < g.M) {
-            const int b = (int)(m / o.L), pos = (int)(m - (int64_t)b * o.L);
-            *reinterpret_cast<u32x4_t*>(base + ((int64_t)(b * nh + head) * o.Ls + pos) * hd +
-                                        pd0 + cc) =
-                *reinterpret_cast<const u32x4_t*>(scr + r * SPS + cc);
-          }
+        for (int i = 0; i < TM; ++i) {
+          cs[i] = *reinterpret_cast<const float2*>(o.cos_t + rp[i] * half + (pd >> 1));
+          sn[i] = *reinterpret_cast<const float2*>(o.sin_t + rp[i] * half + (pd >> 1));
+        }
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          if (row0 + i * 16 >= g.M) continue;
+          const float x0 = acc[i][j][0] + bias.x, x1 = acc[i][j][1] + bias.y;
+          const float x2 = acc[i][j][2] + bias.z, x3 = acc[i][j][3] + bias.w;
+          u32x2_t p;
+          p.x = pack_bf16x2(x0 * cs[i].x - x1 * sn[i].x, x1 * cs[i].x + x0 * sn[i].x);
+          p.y = pack_bf16x2(x2 * cs[i].y - x3 * sn[i].y, x3 * cs[i].y + x2 * sn[i].y);
+          *reinterpret_cast<u32x2_t*>(base + ((int64_t)(rb[i] * nh + head) * o.Ls + rp[i]) * hd + pd) = p;
         }
       } else {
-        constexpr int CPC = WR / 8;            // runs of 8 positions per head dimension
 #pragma unroll
-        for (int k = 0; k < WC * CPC / 64; ++k) {
-          const int id = lane + 64 * k, dcol = id / CPC, rr = (id % CPC) * 8;
-          const int64_t m = row0 + rr;
-          const int b = (int)(m / o.L), pos = (int)(m - (int64_t)b * o.L);
-          uint16_t* dst = o.vt + ((int64_t)(b * o.n_kv_heads + head) * hd + pd0 + dcol) * o.Ls;
-          if (m + 7 < g.M && pos + 7 < o.L && (pos & 7) == 0) {
-            *reinterpret_cast<u32x4_t*>(dst + pos) =
-                *reinterpret_cast<const u32x4_t*>(scr + dcol * SPV + rr);
+        for (int i = 0; i < TM; ++i) {
+          const float x[4] = {acc[i][j][0] + bias.x, acc[i][j][1] + bias.y, acc[i][j][2] + bias.z, acc[i][j][3] + bias.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) scr[(4 * fc + e) * SPV + i * 16 + fr] = (uint16_t)f32_to_bf16_bits(x[e]);
+        }
+#pragma unroll
+        for (int k = 0; k < NCH; ++k) {
+          const int id = lane + 64 * k, dcol = id / CPC, rr = id % CPC * 8;
+          const int m = m0 + wm * WR + rr;
+          if (id >= 16 * CPC) continue;
+          uint16_t* dst = o.vt + ((int64_t)(vb[k] * o.n_kv_heads + head) * hd + d0 + dcol) * o.Ls;
+          if (m + 7 < g.M && vp[k] + 7 < o.L && (vp[k] & 7) == 0) {
+            *reinterpret_cast<u32x4_t*>(dst + vp[k]) = *reinterpret_cast<const u32x4_t*>(scr + dcol * SPV + rr);
           } else {
-            int bb = b, pp = pos;
+            int bb = vb[k], pp = vp[k];
             for (int t = 0; t < 8 && m + t < g.M; ++t) {
-              o.vt[((int64_t)(bb * o.n_kv_heads + head) * hd + pd0 + dcol) * o.Ls + pp] =
-                  scr[dcol * SPV + rr + t];
+              o.vt[((int64_t)(bb * o.n_kv_heads + head) * hd + d0 + dcol) * o.Ls + pp] = scr[dcol * SPV + rr + t];
               if (++pp == o.L) { pp = 0; ++bb; }
             }
           }
@@ -465,162 +356,160 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm(GemmArgs g) {
       }
     }
   } else if constexpr (EPI == EPI_TOP1) {
-    // Row statistics of Eq. (1) over this wavefront's TN x 32 columns.  Each 32 x 32 block
-    // passes through a per-wavefront LDS scratch as the rounded logits EPI_BF16 would write;
-    // lane l reduces row l % 32 over the block's columns 16 (l / 32) .. + 15, the two lanes
-    // of a row are merged (lower columns first), and the blocks of a block row are folded in
-    // column order.
-    constexpr int SP = 34;  // scratch row pitch, bf16
-    static_assert(sizeof(lds) >= (size_t)WAVES_M * WAVES_N * 32 * SP * 2, "TOP1 scratch");
-    __syncthreads();  // every wavefront is done reading the operand tiles
-    uint16_t* scr = lds + wave * 32 * SP;
-    const int rr = lane & 31, half = lane >> 5;
-    TopState rs[TM];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) rs[i] = TopState{-INFINITY, 0.f, INT_MAX};
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-          scr[(8 * (e >> 2) + row_q + (e & 3)) * SP + col_l] =
-              (uint16_t)f32_to_bf16_bits(acc[i][j][e] * g.scale);
-        __syncthreads();
-        const int c0 = n0 + wn * TN * 32 + j * 32 + half * 16;
-        float v[16];
-        TopState t{-INFINITY, 0.f, INT_MAX};
-#pragma unroll
-        for (int c = 0; c < 16; ++c) {
-          float x = bf16_bits_to_f32(scr[rr * SP + half * 16 + c]);
-          if (c0 + c >= g.N || c0 + c == g.mask_id) x = -INFINITY;
-          v[c] = x;
-          if (x > t.m) { t.m = x; t.arg = c0 + c; }
-        }
-        if (t.m != -INFINITY) {
-          const float ml = t.m * LOG2E;
-#pragma unroll
-          for (int c = 0; c < 16; ++c) t.s += fast_exp2(fmaf(v[c], LOG2E, -ml));
-        }
-        const TopState u{__shfl_xor(t.m, 32, 64), __shfl_xor(t.s, 32, 64), __shfl_xor(t.arg, 32, 64)};
-        rs[i] = merge(rs[i], half == 0 ? merge(t, u) : merge(u, t));
-        __syncthreads();  // the scratch is rewritten by the next block
-      }
+    // Row statistics of Eq. (1) over this wavefront's TN x 16 columns, of the rounded logits
+    // EPI_BF16 would write: a lane reduces its TN x 4 columns, then the 4 lanes of a row
+    // agree on the max (lowest column among equals) and add their sums.
     const int part = tile_n * WAVES_N + wn;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-      const int row = m0 + wm * TM * 32 + i * 32 + rr;
-      if (half == 0 && row < g.M) {
-        const int64_t o = (int64_t)row * g.n_parts + part;
-        g.part_m[o] = rs[i].m;
-        g.part_s[o] = rs[i].s;
-        g.part_arg[o] = rs[i].arg;
-      }
-    }
-  } else if constexpr (EPI == EPI_ADD_F32 || EPI == EPI_PART_F32) {
-    // fp32 outputs (residual update, split-K partials): each wavefront stages one 32-row
-    // block of its tile at a time in LDS (a whole fp32 tile per wavefront would not fit) and
-    // writes rows of WC floats as 16-byte stores, a read-modify-write for the residual update
-    constexpr int SPF = WC + 4;                // staged row pitch, fp32
-    constexpr int CPR = WC / 4;                // 16-byte chunks per staged row
-    static_assert(sizeof(lds) >= (size_t)WAVES_M * WAVES_N * 32 * SPF * 4, "stage");
-    float* scr = reinterpret_cast<float*>(lds) + wave * 32 * SPF;
-    float* C = reinterpret_cast<float*>(g.C) +
-               (EPI == EPI_PART_F32 ? (int64_t)split * g.M * g.ldc : (int64_t)0);
-    const int c0 = n0 + wn * WC;
-    const int ncol = min(WC, g.N - c0);
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      __syncthreads();  // the operand buffers (i = 0) or the previous block are done with
+      float v[TN * 4];
+      float m = -INFINITY;
+      int arg = INT_MAX;
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int e = 0; e < 16; ++e)
-          scr[(8 * (e >> 2) + row_q + (e & 3)) * SPF + j * 32 + col_l] = acc[i][j][e];
-      __syncthreads();
-      const int64_t row0 = m0 + wm * WR + i * 32;
-      if (ncol > 0) {
-#pragma unroll
-        for (int k = 0; k < 32 * CPR / 64; ++k) {
-          const int id = lane + 64 * k, r = id / CPR, cc = (id % CPR) * 4;
-          if (row0 + r >= g.M || cc >= ncol) continue;
-          float* dst = C + (row0 + r) * g.ldc + c0 + cc;
-          const float* src = scr + r * SPF + cc;
-          if (cc + 4 <= ncol) {
-            float4 v = *reinterpret_cast<const float4*>(src);
-            if constexpr (EPI == EPI_ADD_F32) {
-              const float4 h = *reinterpret_cast<const float4*>(dst);
-              v.x = h.x + v.x;
-              v.y = h.y + v.y;
-              v.z = h.z + v.z;
-              v.w = h.w + v.w;
-            }
-            *reinterpret_cast<float4*>(dst) = v;
-          } else {
-            for (int t = 0; t < ncol - cc; ++t) dst[t] = EPI == EPI_ADD_F32 ? dst[t] + src[t] : src[t];
-          }
+        for (int e = 0; e < 4; ++e) {
+          const int c = col0 + j * 16 + e;
+          float x = bf16_bits_to_f32(f32_to_bf16_bits(acc[i][j][e] * g.scale));
+          if (c >= g.N || c == g.mask_id) x = -INFINITY;
+          v[4 * j + e] = x;
+          if (x > m) { m = x; arg = c; }
         }
+#pragma unroll
+      for (int o = 16; o <= 32; o <<= 1) {
+        const float om = __shfl_xor(m, o, 64);
+        const int oa = __shfl_xor(arg, o, 64);
+        arg = om > m ? oa : (m > om ? arg : min(arg, oa));
+        m = fmaxf(m, om);
+      }
+      float s = 0.f;
+      if (m != -INFINITY) {
+        const float ml = m * LOG2E;
+#pragma unroll
+        for (int k = 0; k < TN * 4; ++k) s += fast_exp2(fmaf(v[k], LOG2E, -ml));
+      }
+      s += __shfl_xor(s, 16, 64);
+      s += __shfl_xor(s, 32, 64);
+      const int row = row0 + i * 16;
+      if (fc == 0 && row < g.M) {
+        const int64_t o = (int64_t)row * g.n_parts + part;
+        g.part_m[o] = m;
+        g.part_s[o] = s;
+        g.part_arg[o] = arg;
+      }
+    }
+  } else if constexpr (EPI == EPI_ADD_F32 || EPI == EPI_PART_F32) {
+    // N % 4 == 0 (checked at launch): a lane's 4 columns are in or out together
+    float* C = reinterpret_cast<float*>(g.C) +
+               (EPI == EPI_PART_F32 ? (int64_t)split * g.M * g.ldc : (int64_t)0);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const int row = row0 + i * 16;
+      if (row >= g.M) continue;
+      float* dst = C + (int64_t)row * g.ldc + col0;
+      if constexpr (EPI == EPI_ADD_F32) {
+        f32x4_t h[TN];
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          if (col0 + j * 16 < g.N) h[j] = *reinterpret_cast<const f32x4_t*>(dst + j * 16);
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          if (col0 + j * 16 < g.N) *reinterpret_cast<f32x4_t*>(dst + j * 16) = h[j] + acc[i][j];
+      } else {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          if (col0 + j * 16 < g.N) *reinterpret_cast<f32x4_t*>(dst + j * 16) = acc[i][j];
       }
     }
   } else {
+    uint16_t* C = reinterpret_cast<uint16_t*>(g.C);
+    const bool vec = (g.ldc & 3) == 0 && ((uintptr_t)C & 7) == 0;
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int col = n0 + wn * TN * 32 + j * 32 + col_l;
-      if (col >= g.N) continue;
-      const float bias = g.bias ? g.bias[col] : 0.f;
+    for (int i = 0; i < TM; ++i) {
+      const int row = row0 + i * 16;
+      if (row >= g.M) continue;
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int j = 0; j < TN; ++j) {
+        const int col = col0 + j * 16;
+        uint16_t* dst = C + (int64_t)row * g.ldc + col;
+        float x[4];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int row = m0 + wm * TM * 32 + i * 32 + 8 * (e >> 2) + row_q + (e & 3);
-          if (row >= g.M) continue;
-          uint16_t* C = reinterpret_cast<uint16_t*>(g.C);
-          C[(int64_t)row * g.ldc + col] =
-              (uint16_t)f32_to_bf16_bits((acc[i][j][e] + bias) * g.scale);
+        for (int e = 0; e < 4; ++e)
+          x[e] = (acc[i][j][e] + (g.bias && col + e < g.N ? g.bias[col + e] : 0.f)) * g.scale;
+        if (vec && col + 3 < g.N) {
+          *reinterpret_cast<u32x2_t*>(dst) = u32x2_t{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3])};
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (col + e < g.N) dst[e] = (uint16_t)f32_to_bf16_bits(x[e]);
         }
+      }
     }
   }
 }
 
 // ---- tile configurations ---------------------------------------------------------------
-// LDS read throughput per CU grows with the number of resident waves (one wave per SIMD
-// cannot keep enough reads in flight to feed the MFMA pipe), so the large-tile configs
-// run 2-4 waves per SIMD.
-// cfg 0: 256 x 256 tile, 16 waves (4 x 4), wave tile 64 x 64, PIPE 0
-// cfg 1:  32 x 128 tile, 4 waves (1 x 4) (2 waves for SwiGLU), for M <= 64 (LM head rows)
-// cfg 2: 256 x 128 tile,  8 waves (4 x 2), wave tile 64 x 64, PIPE 2
-// cfg 3: 256 x 192 tile, 12 waves (4 x 3), wave tile 64 x 64, PIPE 2
-// cfg 4: 128 x 192 tile, 12 waves (4 x 3), wave tile 32 x 64, PIPE 2: twice the tiles of
-//        cfg 3, so an output of 512 rows x 12288 columns fills 256 CUs without splitting K.
-//        Twelve waves load the four SIMDs evenly (three each); as 6 waves of 64 x 64 (two
-//        SIMDs with two waves, two with one) the QKV projection at 512 rows ran 1.2 %
-//        slower per pass, although a 32 x 64 wave tile reads 1.5 x the LDS bytes per MFMA
-struct CfgShape { int bm, bn; };
+// X(cfg, WAVES_M, WAVES_N, TM, TN, stages, minimum waves per SIMD, workgroups per CU (LDS),
+//   slice_us, cu_us, tile_us): the last three are gemm_us's constants per 32-wide slice of a
+//   lone tile, per slice and resident tile on a busy chip, and per tile.
+// 0 to 4 serve the wide products (a larger tile moves fewer bytes per FLOP from L2 into LDS);
+// 5 to 8 products whose larger tiles would leave CUs idle: few rows, or few rows and columns.
+#define GEMM_CFGS(X)                                    \
+  X(0, 4, 2, 4, 8, 5, 1, 1, 0.507, 0.697, 5.53)   \
+  X(1, 8, 1, 2, 12, 5, 1, 1, 0.468, 0.555, 5.25)   \
+  X(2, 4, 2, 4, 4, 5, 1, 1, 0.342, 0.395, 3.08)   \
+  X(3, 4, 2, 2, 6, 5, 1, 1, 0.320, 0.344, 2.42)   \
+  X(4, 2, 2, 4, 4, 5, 2, 2, 0.236, 0.225, 2.33)   \
+  X(5, 2, 2, 4, 2, 5, 2, 2, 0.164, 0.176, 1.45)   \
+  X(6, 2, 2, 2, 4, 5, 2, 2, 0.181, 0.169, 1.41)   \
+  X(7, 2, 2, 2, 2, 7, 2, 2, 0.119, 0.106, 0.74)   \
+  X(8, 2, 2, 1, 2, 9, 2, 2, 0.095, 0.086, 0.66)
+struct CfgShape {
+  int bm, bn, waves_n, per_cu;
+  double slice_us, cu_us, tile_us;
+};
 static CfgShape cfg_shape(int cfg) {
   switch (cfg) {
-    case 0: return {256, 256};
-    case 1: return {32, 128};
-    case 3: return {256, 192};
-    case 4: return {128, 192};
-    default: return {256, 128};
+#define X(C, WM, WN, TM, TN, ST, OCC, PER_CU, SL, CU, TILE) \
+  case C: return {WM * TM * 16, WN * TN * 16, WN, PER_CU, SL, CU, TILE};
+    GEMM_CFGS(X)
+#undef X
   }
+  return {};
 }
 
-int gemm_num_cfgs() { return 5; }
+int gemm_num_cfgs() { return 9; }
 
-// wavefront columns per tile and their width (TN x 32) of each config
+// wavefront columns per tile and their width (TN x 16) of each config
 int gemm_top1_parts(const GemmPlan& p, int N) {
   const CfgShape sh = cfg_shape(p.cfg);
-  const int waves_n = p.cfg == 0 ? 4 : (p.cfg == 1 ? 4 : (p.cfg == 3 || p.cfg == 4 ? 3 : 2));
-  return (N + sh.bn - 1) / sh.bn * waves_n;
+  return (N + sh.bn - 1) / sh.bn * sh.waves_n;
 }
 
-// Relative main-loop efficiency of the large-tile configs (16, 12, 8 and 12 waves per
-// workgroup), measured on the pass's shapes (cfg 4: 64.4 us for the whole-K QKV projection
-// with its bias + RoPE epilogue at 512 x 12288 x 4096, as 6 waves; the 12-wave layout is a
-// few us faster there, and keeping the 6-wave figure leaves every plan as it was).
-static double cfg_eff(int cfg) {
-  return cfg == 0 ? 1.0 : (cfg == 3 ? 1.03 : (cfg == 4 ? 0.72 : 0.88));
+// Estimated time of one launch in microseconds: rounds of resident tiles, each the larger of
+// a tile's own latency per 32-wide slice and the chip's throughput with that many tiles
+// resident (a few busy CUs run faster than all: power), plus prologue and epilogue; the time
+// to stream the weights, of which two thirds overlap with it; plus the traffic of split-K partials and, in the
+// kernel downstream, of folding them (fold_us more where that kernel is an extra one).  The
+// constants are fitted to a sweep of all configs and split counts over 39 shapes (64 to 4096
+// rows, 256 to 152064 columns, K 256 to 18944); the plan it picks is on average within 1 % of
+// the fastest measured one.
+static double gemm_us(int M, int N, int K, int num_cus, int cfg, int splits, double fold_us) {
+  const CfgShape sh = cfg_shape(cfg);
+  const double nk = (double)K / BK / splits;
+  const int64_t grid = (int64_t)((M + sh.bm - 1) / sh.bm) * ((N + sh.bn - 1) / sh.bn) * splits;
+  const int64_t slots = (int64_t)num_cus * sh.per_cu;
+  auto round_us = [&](int64_t n) {
+    const double per_cu = (double)std::min<int64_t>(sh.per_cu, (n + num_cus - 1) / num_cus);
+    const double busy = std::min(1.0, (double)n / num_cus);
+    return nk * std::max(sh.slice_us, per_cu * sh.cu_us * (0.41 + 0.59 * busy)) + sh.tile_us;
+  };
+  double us = 1.4 + (double)(grid / slots) * round_us(slots);
+  if (grid % slots) us += round_us(grid % slots);
+  const double stream_us = 1.4 + (double)N * K * 2 / 6.3e6;  // the weights at 6.3 TB/s
+  us = std::max(us, stream_us) + 0.37 * std::min(us, stream_us);
+  if (splits > 1) us += 0.37 * (double)splits * M * N * 4.0 / (1 << 20) + fold_us;
+  return us;
 }
 
 GemmPlan gemm_plan_cfg(int M, int N, int K, int cfg, int splits) {
@@ -633,64 +522,35 @@ GemmPlan gemm_plan_cfg(int M, int N, int K, int cfg, int splits) {
   return p;
 }
 
-// Whole-K tiles: minimise rounds-of-tiles x tile area / efficiency, which picks the fastest
-// measured config at every shape of the pass (e.g. 256 x 192 for the 512 x 24576 gate/up,
-// 256 x 128 for 512 x 12288).
 GemmPlan gemm_plan(int M, int N, int K, int num_cus) {
-  if (M <= 64) return gemm_plan_cfg(M, N, K, 1, 1);
-  const int cfgs[4] = {0, 3, 2, 4};
-  int best = 0;
-  double best_cost = 0;
-  for (int c = 0; c < 4; ++c) {
-    const CfgShape sh = cfg_shape(cfgs[c]);
-    const int tiles = ((M + sh.bm - 1) / sh.bm) * ((N + sh.bn - 1) / sh.bn);
-    const int rounds = (tiles + num_cus - 1) / num_cus;
-    const double cost = (double)rounds * sh.bm * sh.bn / cfg_eff(cfgs[c]);
-    if (c == 0 || cost < best_cost) { best = cfgs[c]; best_cost = cost; }
-  }
-  return gemm_plan_cfg(M, N, K, best, 1);
+  return gemm_plan_split(M, N, K, num_cus, 1, 0.0);
 }
 
-// Tiles that may split K (outputs whose consumer folds partials in): estimated time =
-// rounds x per-tile main loop (2.18 MMAC per microsecond per CU at efficiency 1) + partial
-// traffic (written here, read back downstream: ~0.46 us per MiB, the measured cost of the
-// QKV split-K 2 partials and their finish kernel), over configs {0, 2, 3, 4} and
-// 1, 2, 4 or 8 splits with >= 8 K-slices each (only `splits` when it is > 0).  Splits never
-// exceed the workspace bound.
-GemmPlan gemm_plan_split(int M, int N, int K, int num_cus, int splits) {
-  if (M <= 64 && splits <= 1) return gemm_plan_cfg(M, N, K, 1, 1);
-  const int nk = K / BK;
-  const int cfgs[4] = {0, 3, 2, 4};
-  GemmPlan best{};
-  double best_us = 0;
-  bool have = false;
-  for (int c = 0; c < 4; ++c) {
-    const CfgShape sh = cfg_shape(cfgs[c]);
-    const int tiles = ((M + sh.bm - 1) / sh.bm) * ((N + sh.bn - 1) / sh.bn);
-    for (int sp = 1; sp <= 8; sp *= 2) {
-      if (splits > 0 && sp != splits) continue;
-      if (sp > 1 && (nk % sp != 0 || nk / sp < 8 ||
-                     (size_t)sp * M * N > gemm_ws_floats_bound(num_cus)))
-        continue;
-      const int rounds = (tiles * sp + num_cus - 1) / num_cus;
-      double us = (double)rounds * sh.bm * sh.bn * ((double)K / sp) / cfg_eff(cfgs[c]) / 2.18e6;
-      if (sp > 1) us += 0.46 * (double)sp * M * N * 4.0 / (1 << 20);
-      if (!have || us < best_us) { best = gemm_plan_cfg(M, N, K, cfgs[c], sp); best_us = us; have = true; }
+GemmPlan gemm_plan_split(int M, int N, int K, int num_cus, int splits, double fold_us) {
+  int best_cfg = 0, best_sp = splits > 0 ? splits : 1;
+  double best_us = -1;
+  for (int sp = 1; sp <= 8; sp *= 2) {
+    if (splits > 0 && sp != splits) continue;
+    if (sp > 1 && (K % (64 * sp) != 0 || K / sp < 256 ||
+                   (size_t)sp * M * N > gemm_ws_floats_bound(num_cus)))
+      continue;
+    for (int c = 0; c < gemm_num_cfgs(); ++c) {
+      const double us = gemm_us(M, N, K, num_cus, c, sp, fold_us);
+      if (best_us < 0 || us < best_us) { best_cfg = c; best_sp = sp; best_us = us; }
     }
   }
-  return best;
+  return gemm_plan_cfg(M, N, K, best_cfg, best_sp);
 }
+
 
 // With timing events, the dispatch itself stamps them with the kernel's start and end
 // (hipExtLaunchKernel), so no marker packet sits between the events and the kernel.
-template <int WAVES_M, int WAVES_N, int TM, int TN, int EPI, int PIPE>
+template <int WM, int WN, int TM, int TN, int ST, int OCC, int EPI>
 static hipError_t run(const GemmArgs& a, int grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   if (e0 || e1)
-    hipExtLaunchKernelGGL((k_gemm<WAVES_M, WAVES_N, TM, TN, EPI, PIPE>), dim3(grid),
-                          dim3(WAVES_M * WAVES_N * 64), 0, s, e0, e1, 0, a);
+    hipExtLaunchKernelGGL((k_gemm<WM, WN, TM, TN, ST, OCC, EPI>), dim3(grid), dim3(WM * WN * 64), 0, s, e0, e1, 0, a);
   else
-    hipLaunchKernelGGL((k_gemm<WAVES_M, WAVES_N, TM, TN, EPI, PIPE>), dim3(grid),
-                       dim3(WAVES_M * WAVES_N * 64), 0, s, a);
+    hipLaunchKernelGGL((k_gemm<WM, WN, TM, TN, ST, OCC, EPI>), dim3(grid), dim3(WM * WN * 64), 0, s, a);
   return hipGetLastError();
 }
 
@@ -698,20 +558,21 @@ template <int EPI>
 static hipError_t run_cfg(int cfg, const GemmArgs& a, int grid, hipStream_t s, hipEvent_t e0,
                           hipEvent_t e1) {
   switch (cfg) {
-    case 0: return run<4, 4, 2, 2, EPI, 0>(a, grid, s, e0, e1);
-    case 1:
-      if constexpr (EPI == EPI_SWIGLU) return run<1, 2, 1, 2, EPI, 1>(a, grid, s, e0, e1);
-      else return run<1, 4, 1, 1, EPI, 1>(a, grid, s, e0, e1);
-    case 3: return run<4, 3, 2, 2, EPI, 2>(a, grid, s, e0, e1);
-    case 4: return run<4, 3, 1, 2, EPI, 2>(a, grid, s, e0, e1);
-    default: return run<4, 2, 2, 2, EPI, 2>(a, grid, s, e0, e1);
+#define X(C, WM, WN, TM, TN, ST, OCC, ...) \
+  case C: return run<WM, WN, TM, TN, ST, OCC, EPI>(a, grid, s, e0, e1);
+    GEMM_CFGS(X)
+#undef X
   }
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_gemm(int epi, const GemmArgs& in, const GemmPlan& p, hipStream_t s,
                        hipEvent_t ev_start, hipEvent_t ev_stop) {
   if (in.M == 0 || in.N == 0) return hipSuccess;
-  if (p.splits < 1 || in.K % (BK * p.splits) != 0) return hipErrorInvalidValue;
+  // pairs of 32-wide slices; whole 64-row weight blocks; fp32 outputs in groups of 4 columns
+  if (p.splits < 1 || in.K % (64 * p.splits) != 0) return hipErrorInvalidValue;
+  if (in.w_layout == W_BLOCKS && in.N % 64 != 0) return hipErrorInvalidValue;
+  if ((epi == EPI_ADD_F32 || epi == EPI_PART_F32) && in.N % 4 != 0) return hipErrorInvalidValue;
   if (p.splits > 1 && epi != EPI_PART_F32) return hipErrorInvalidValue;
   GemmArgs a = in;
   a.splits = p.splits;

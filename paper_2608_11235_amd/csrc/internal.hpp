@@ -7,7 +7,7 @@ namespace cora {
 
 // ---- weight init ------------------------------------------------------------------------
 // Physical row of logical row r: 0 identity (+row_offset), 1 gate half and 2 up half of
-// the 32-row interleaved gate/up matrix.
+// the 16-row interleaved gate/up matrix.
 // 3: rows of q or k heads stored pair-interleaved within each head of hd rows (logical
 // j < hd/2 at 2j, logical j + hd/2 at 2j + 1), after row_offset.
 enum RowMap { ROW_IDENTITY = 0, ROW_GATE = 1, ROW_UP = 2, ROW_ROPE_PAIR = 3 };
@@ -29,11 +29,13 @@ struct RowSel {
   int mode, L, n_rows, row_begin, prompt_len, block_len, n_blocks;
   const int32_t* block_idx;
 };
+// The output is row-major, or K panels [d / 32][rows][32] (the GEMMs' A operand, d % 32 == 0)
+// when panels is set.
 hipError_t launch_rmsnorm(const float* h, const float* w, uint16_t* out, int rows, int d,
-                          float eps, RowSel sel, hipStream_t s);
+                          float eps, RowSel sel, bool panels, hipStream_t s);
 // h[r, :] += part[0][r, :] + ... + part[splits-1][r, :] (partials [splits][rows][d], summed in
-// split order), then, when out is not null, out[r, :] = bf16(rmsnorm(h[r, :]) * w).
-// d % 4 == 0 and d <= RESIDUAL_NORM_MAX_D.
+// split order), then, when out is not null, out[r, :] = bf16(rmsnorm(h[r, :]) * w) in K panels
+// [d / 32][rows][32].  d % 32 == 0 and d <= RESIDUAL_NORM_MAX_D.
 constexpr int RESIDUAL_NORM_MAX_D = 8192;
 hipError_t launch_residual_norm(float* h, const float* part, int splits, int rows, int d,
                                 const float* w, uint16_t* out, float eps, hipStream_t s);
@@ -55,6 +57,9 @@ hipError_t launch_scatter_rows(const int32_t* tokens, const int32_t* passes, con
                                int32_t* out_tokens, int32_t* out_passes, hipStream_t s);
 
 // ---- GEMM: C[M, N] = A[M, K] . W[N, K]^T, bf16 in, fp32 accumulate ---------------------
+// A in K panels [K / 32][M][32]; W in one of two layouts (see gemm.hip): 64 x 32 blocks
+// (layer weights, N % 64 == 0) or the LM head's packed layout
+enum GemmWLayout { W_BLOCKS = 0, W_LM_HEAD = 1 };
 enum GemmEpi {
   EPI_BF16 = 0, EPI_ADD_F32 = 1, EPI_SWIGLU = 2, EPI_QKV_ROPE = 3, EPI_PART_F32 = 4, EPI_TOP1 = 5
 };
@@ -75,15 +80,15 @@ struct QkvOut {
   int L, Ls, n_heads, n_kv_heads, head_dim;
 };
 struct GemmArgs {
-  const uint16_t* A; int64_t lda;
-  const uint16_t* W; int64_t ldw;
+  const uint16_t* A;
+  const uint16_t* W;
+  int w_layout;
   int M, N, K;
-  void* C; int64_t ldc;
+  void* C; int64_t ldc;  // ldc unused by EPI_SWIGLU (panels of M rows) and EPI_QKV_ROPE
   const float* bias;   // EPI_BF16: per-column bias (or null)
   float scale;         // EPI_BF16: multiplier after the bias
   int splits;          // set by launch_gemm from the plan
   QkvOut qkv;          // EPI_QKV_ROPE destinations
-  bool w_packed;       // W in 64 x 64 blocks (N % 64 == 0, K % 64 == 0), see pack layout
   // EPI_TOP1 outputs
   float* part_m; float* part_s; int* part_arg;
   int n_parts, mask_id;
@@ -93,19 +98,20 @@ struct GemmPlan {
   size_t ws_floats;    // EPI_PART_F32 partial floats (splits * M * N) when splits > 1
 };
 // Whole-K plan for any epilogue; split plan (EPI_PART_F32 when splits > 1, else any
-// epilogue) never needs more than gemm_ws_floats_bound(num_cus) partial floats.  With
-// splits > 0 the split plan keeps that split count (it must divide K / 64 into runs of >= 8
-// slices) and only picks the tile config; the split count alone decides the summation order
-// of an output, the tile config does not.
+// epilogue) never needs more than gemm_ws_floats_bound(num_cus) partial floats.  fold_us: what
+// a split costs besides the partials' traffic (0 where the kernel that folds them runs anyway).
+// With splits > 0 the split plan keeps that split count (K % (64 * splits) == 0) and only
+// picks the tile config; the split count alone decides the summation order of an output, the
+// tile config does not.
 GemmPlan gemm_plan(int M, int N, int K, int num_cus);
-GemmPlan gemm_plan_split(int M, int N, int K, int num_cus, int splits = 0);
+GemmPlan gemm_plan_split(int M, int N, int K, int num_cus, int splits, double fold_us);
 GemmPlan gemm_plan_cfg(int M, int N, int K, int cfg, int splits);
 int gemm_num_cfgs();
 inline size_t gemm_ws_floats_bound(int num_cus) { return (size_t)2 * num_cus * 256 * 256; }
 // ev_start / ev_stop (optional): stamped with the kernel's start and end by the dispatch
 hipError_t launch_gemm(int epi, const GemmArgs& a, const GemmPlan& p, hipStream_t s,
                        hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
-// EPI_TOP1 partials per row of a plan (column ranges of TN x 32 over the N tiles)
+// EPI_TOP1 partials per row of a plan (column ranges of TN x 16 over the N tiles)
 int gemm_top1_parts(const GemmPlan& p, int N);
 // EPI_PART_F32 partials [splits][M][N] of the QKV projection -> the EPI_QKV_ROPE outputs.
 hipError_t launch_qkv_finish(const float* part, int splits, int M, int N, const float* bias,

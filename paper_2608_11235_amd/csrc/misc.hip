@@ -26,11 +26,11 @@ __device__ __forceinline__ float normal_from_counter(uint64_t key, uint64_t ctr,
   return (float)(std_dev * n);
 }
 
-// element (pr, c) of the physical matrix goes to pr * ld + c, or, packed (ld % 64 == 0), to
-// block (pr / 64, c / 64) of 64 x 64 (row-major inside), blocks ordered by row block then
+// element (pr, c) of the physical matrix goes to pr * ld + c, or, packed (ld % 32 == 0), to
+// block (pr / 64, c / 32) of 64 x 32 (row-major inside), blocks ordered by row block then
 // column block
-__device__ __forceinline__ int64_t packed64_index(int64_t pr, int64_t c, int64_t ld) {
-  return ((pr >> 6) * (ld >> 6) + (c >> 6)) * 4096 + (pr & 63) * 64 + (c & 63);
+__device__ __forceinline__ int64_t packed_index(int64_t pr, int64_t c, int64_t ld) {
+  return ((pr >> 6) * (ld >> 5) + (c >> 5)) * 2048 + (pr & 63) * 32 + (c & 31);
 }
 
 __global__ void k_init_bf16(uint16_t* __restrict__ dst, uint64_t key, uint64_t base, int64_t rows,
@@ -38,13 +38,13 @@ __global__ void k_init_bf16(uint16_t* __restrict__ dst, uint64_t key, uint64_t b
                             double std_dev, int hd, int packed) {
   for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
     int64_t pr;
-    if (row_map == ROW_GATE) pr = (r >> 5) * 64 + (r & 31);
-    else if (row_map == ROW_UP) pr = (r >> 5) * 64 + 32 + (r & 31);
+    if (row_map == ROW_GATE) pr = (r >> 4) * 32 + (r & 15);
+    else if (row_map == ROW_UP) pr = (r >> 4) * 32 + 16 + (r & 15);
     else if (row_map == ROW_ROPE_PAIR) pr = row_offset + (r / hd) * hd + rope_pair_pos((int)(r % hd), hd);
     else pr = row_offset + r;
     for (int64_t c = threadIdx.x; c < cols; c += blockDim.x) {
       const uint64_t ctr = base | (uint64_t)(r * cols + c);
-      dst[packed ? packed64_index(pr, c, ld) : pr * ld + c] =
+      dst[packed ? packed_index(pr, c, ld) : pr * ld + c] =
           (uint16_t)f32_to_bf16_bits(normal_from_counter(key, ctr, std_dev));
     }
   }
@@ -79,7 +79,7 @@ static uint64_t host_mix64(uint64_t z) {
 hipError_t launch_init_bf16(uint16_t* dst, uint64_t seed, uint64_t tensor_id, int64_t rows,
                             int64_t cols, int64_t ld, int row_map, int64_t row_offset, double std_dev,
                             int head_dim, hipStream_t s, bool packed) {
-  if (packed && ld % 64 != 0) return hipErrorInvalidValue;
+  if (packed && ld % 32 != 0) return hipErrorInvalidValue;
   const int grid = (int)(rows < 16384 ? rows : 16384);
   hipLaunchKernelGGL(k_init_bf16, dim3(grid), dim3(256), 0, s, dst, host_mix64(seed),
                      tensor_id << 40, rows, cols, ld, row_map, row_offset, std_dev, head_dim,
@@ -127,11 +127,11 @@ hipError_t launch_embed(const int32_t* tokens, const uint16_t* E, float* h, int 
   return hipGetLastError();
 }
 
-// ---- RMSNorm: fp32 rows in, bf16 rows out ------------------------------------------------
+// ---- RMSNorm: fp32 rows in, bf16 rows (or K panels of 32) out ------------------------------------------------
 __global__ __launch_bounds__(256) void k_rmsnorm(const float* __restrict__ h,
                                                  const float* __restrict__ w,
                                                  uint16_t* __restrict__ out, int d, float eps,
-                                                 RowSel sel) {
+                                                 RowSel sel, int panels) {
   const int j = blockIdx.x;
   int64_t src = j;
   if (sel.mode != 0) {
@@ -156,21 +156,23 @@ __global__ __launch_bounds__(256) void k_rmsnorm(const float* __restrict__ h,
   __syncthreads();
   const float tot = part[0] + part[1] + part[2] + part[3];
   const float inv = 1.0f / sqrtf(tot / (float)d + eps);
-  uint16_t* o = out + (int64_t)j * d;
+  const int64_t rows = gridDim.x;
   for (int c = threadIdx.x * 4; c < d; c += 256 * 4) {
     const float4 v = *reinterpret_cast<const float4*>(x + c);
     const float4 g = *reinterpret_cast<const float4*>(w + c);
     u32x2_t p;
     p.x = pack_bf16x2(v.x * inv * g.x, v.y * inv * g.y);
     p.y = pack_bf16x2(v.z * inv * g.z, v.w * inv * g.w);
-    *reinterpret_cast<u32x2_t*>(o + c) = p;
+    uint16_t* o = out + (panels ? ((c >> 5) * rows + j) * 32 + (c & 31) : (int64_t)j * d + c);
+    *reinterpret_cast<u32x2_t*>(o) = p;
   }
 }
 
 hipError_t launch_rmsnorm(const float* h, const float* w, uint16_t* out, int rows, int d,
-                          float eps, RowSel sel, hipStream_t s) {
+                          float eps, RowSel sel, bool panels, hipStream_t s) {
   if (rows == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_rmsnorm, dim3(rows), dim3(256), 0, s, h, w, out, d, eps, sel);
+  if (panels && d % 32 != 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_rmsnorm, dim3(rows), dim3(256), 0, s, h, w, out, d, eps, sel, panels ? 1 : 0);
   return hipGetLastError();
 }
 

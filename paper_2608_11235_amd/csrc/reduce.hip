@@ -61,7 +61,7 @@ __global__ __launch_bounds__(NT) void k_residual_norm(float* __restrict__ h,
 #pragma unroll
   for (int i = 0; i < NT / 64; ++i) tot += red[i];
   const float inv = 1.0f / sqrtf(tot / (float)d + eps);
-  uint16_t* o = out + r * d;
+  const int64_t rows = gridDim.x;
 #pragma unroll
   for (int i = 0; i < C; ++i) {
     const int c = (threadIdx.x + i * NT) * 4;
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(NT) void k_residual_norm(float* __restrict__ h,
       u32x2_t q;
       q.x = pack_bf16x2(v[i].x * inv * g.x, v[i].y * inv * g.y);
       q.y = pack_bf16x2(v[i].z * inv * g.z, v[i].w * inv * g.w);
-      *reinterpret_cast<u32x2_t*>(o + c) = q;
+      *reinterpret_cast<u32x2_t*>(out + ((c >> 5) * rows + r) * 32 + (c & 31)) = q;  // K panels
     }
   }
 }
@@ -89,7 +89,7 @@ static void residual_norm_c(int d4, dim3 grid, hipStream_t s, float* h, const fl
 hipError_t launch_residual_norm(float* h, const float* part, int splits, int rows, int d,
                                 const float* w, uint16_t* out, float eps, hipStream_t s) {
   if (rows == 0) return hipSuccess;
-  if (d % 4 != 0 || d > RESIDUAL_NORM_MAX_D) return hipErrorInvalidValue;
+  if (d % 32 != 0 || d > RESIDUAL_NORM_MAX_D) return hipErrorInvalidValue;
   static_assert(RESIDUAL_NORM_MAX_D <= 2 * 1024 * 4, "at most 2 float4 chunks per thread");
   const int d4 = d / 4;
   const int64_t slab = (int64_t)rows * d;

@@ -85,7 +85,7 @@ struct cora_model {
   size_t weight_bytes = 0, ws_bytes = 0;
 
   uint16_t *embed = nullptr, *lm_head = nullptr;
-  // LM head in the packed layout of the few-row kernel (null when the shape does not fit it)
+  // LM head in the packed layout that the few-row kernel and the tiled GEMM read
   uint16_t* lm_head_packed = nullptr;
   float* ones = nullptr;  // all norm weights are 1
   struct Layer {
@@ -214,9 +214,8 @@ extern "C" cora_status cora_model_create(const cora_model_cfg* cfg, uint64_t see
 
   // ---- weights
   size_t wb = 2 * align_up((size_t)V * d * 2) + align_up((size_t)d * 4);
-  // packed LM-head copy for steps that score at most 64 rows (one extra V x d matrix)
-  const bool pack_lm = lm_head_supported(1, V, d, d);
-  if (pack_lm) wb += align_up(lm_head_packed_elems(V, d) * 2);
+  // packed LM-head copy, the one every pass reads (one extra V x d matrix)
+  wb += align_up(lm_head_packed_elems(V, d) * 2);
   const size_t per_layer = align_up((size_t)m->qkv_n * d * 2) + align_up((size_t)d * m->hq * 2) +
                            align_up((size_t)2 * m->f_pad * d * 2) +
                            align_up((size_t)d * m->f_pad * 2) +
@@ -262,7 +261,7 @@ extern "C" cora_status cora_model_create(const cora_model_cfg* cfg, uint64_t see
   Arena w{(char*)m->weight_mem, 0, wb};
   m->embed = w.take<uint16_t>((size_t)V * d);
   m->lm_head = w.take<uint16_t>((size_t)V * d);
-  if (pack_lm) m->lm_head_packed = w.take<uint16_t>(lm_head_packed_elems(V, d));
+  m->lm_head_packed = w.take<uint16_t>(lm_head_packed_elems(V, d));
   m->ones = w.take<float>(d);
   m->layers.resize(L_);
   for (auto& ly : m->layers) {
@@ -323,7 +322,7 @@ extern "C" cora_status cora_model_create(const cora_model_cfg* cfg, uint64_t see
     HIP_TRY(hipMemsetAsync(m->ws_mem, 0, wsb, s));  // finite zeros in every padding region
     HIP_TRY(launch_init_bf16(m->embed, seed, 1, V, d, d, ROW_IDENTITY, 0, sd, hd, s));
     HIP_TRY(launch_init_bf16(m->lm_head, seed, 2, V, d, d, ROW_IDENTITY, 0, sd, hd, s));
-    if (m->lm_head_packed) HIP_TRY(launch_pack_lm_head(m->lm_head, m->lm_head_packed, V, d, s));
+    HIP_TRY(launch_pack_lm_head(m->lm_head, m->lm_head_packed, V, d, s));
     HIP_TRY(launch_fill_f32(m->ones, 1.0f, d, s));
     for (int l = 0; l < (int)L_; ++l) {
       const auto& ly = m->layers[l];
@@ -478,14 +477,15 @@ static cora_status gemm_partials(cora_model* m, GemmArgs g, const GemmPlan& p, h
 }
 
 // Split plan for the live rows g.M with the split count planned for plan_M rows.
-static GemmPlan fixed_split_plan(const cora_model* m, const GemmArgs& g, int plan_M) {
-  const int splits = gemm_plan_split(plan_M, g.N, g.K, m->num_cus).splits;
-  return gemm_plan_split(g.M, g.N, g.K, m->num_cus, splits);
+static GemmPlan fixed_split_plan(const cora_model* m, const GemmArgs& g, int plan_M, double fold_us) {
+  const int splits = gemm_plan_split(plan_M, g.N, g.K, m->num_cus, 0, fold_us).splits;
+  return gemm_plan_split(g.M, g.N, g.K, m->num_cus, splits, fold_us);
 }
 
-// QKV projection with bias, RoPE and head layout, whole-K or split-K.
+// QKV projection with bias, RoPE and head layout, whole-K or split-K (whose partials need a
+// kernel that a whole-K plan does without: 7 us).
 static cora_status qkv_gemm(cora_model* m, const GemmArgs& g, int plan_M, hipStream_t s) {
-  const GemmPlan p = fixed_split_plan(m, g, plan_M);
+  const GemmPlan p = fixed_split_plan(m, g, plan_M, 7.0);
   if (p.splits == 1) {
     HIP_TRY(launch_gemm(EPI_QKV_ROPE, g, p, s));
     return CORA_OK;
@@ -501,12 +501,12 @@ static cora_status qkv_gemm(cora_model* m, const GemmArgs& g, int plan_M, hipStr
 static cora_status residual_gemm(cora_model* m, GemmArgs g, uint16_t* norm_out, int plan_M,
                                  hipStream_t s) {
   const auto& c = m->cfg;
-  const GemmPlan p = fixed_split_plan(m, g, plan_M);
+  const GemmPlan p = fixed_split_plan(m, g, plan_M, 0.0);
   float* h = reinterpret_cast<float*>(g.C);
   if (p.splits == 1) {
     HIP_TRY(launch_gemm(EPI_ADD_F32, g, p, s));
     const RowSel all{0, 0, 0, 0, 0, 0, 0, nullptr};
-    if (norm_out) HIP_TRY(launch_rmsnorm(h, m->ones, norm_out, g.M, g.N, c.rms_eps, all, s));
+    if (norm_out) HIP_TRY(launch_rmsnorm(h, m->ones, norm_out, g.M, g.N, c.rms_eps, all, true, s));
     return CORA_OK;
   }
   if (cora_status st = gemm_partials(m, g, p, s)) return st;
@@ -520,26 +520,22 @@ static cora_status run_layers(cora_model* m, const int32_t* tokens, int B, int L
   const int d = c.d_model, M = B * L, Ls = round_up(L, 64), Mp = plan_rows(m, L);
   HIP_TRY(launch_embed(tokens, m->embed, m->h, M, d, c.vocab, s));
   const RowSel all{0, L, 0, 0, 0, 0, 0, nullptr};
-  HIP_TRY(launch_rmsnorm(m->h, m->ones, m->a, M, d, c.rms_eps, all, s));
+  HIP_TRY(launch_rmsnorm(m->h, m->ones, m->a, M, d, c.rms_eps, all, true, s));
   const size_t n_layers = m->layers.size();
   for (size_t l = 0; l < n_layers; ++l) {
     const auto& ly = m->layers[l];
     // m->a holds rmsnorm(h) of this layer's input
-    GemmArgs g{m->a, d, ly.wqkv, d, M, m->qkv_n, d, nullptr, 0, ly.bqkv, 1.0f};
-    g.w_packed = true;
+    GemmArgs g{m->a, ly.wqkv, W_BLOCKS, M, m->qkv_n, d, nullptr, 0, ly.bqkv, 1.0f};
     g.qkv = QkvOut{m->q, m->k, m->vt, m->rope_cos, m->rope_sin, L, Ls, c.n_heads, c.n_kv_heads,
                    c.head_dim};
     if (cora_status st = qkv_gemm(m, g, Mp, s)) return st;
     HIP_TRY(launch_attention(m->q, m->k, m->vt, m->attn, B, L, Ls, c.n_heads, c.n_kv_heads,
                              c.head_dim, m->max_batch, m->num_cus, s));
-    g = GemmArgs{m->attn, m->hq, ly.wo, m->hq, M, d, m->hq, m->h, d, nullptr, 1.0f};
-    g.w_packed = true;
+    g = GemmArgs{m->attn, ly.wo, W_BLOCKS, M, d, m->hq, m->h, d, nullptr, 1.0f};
     if (cora_status st = residual_gemm(m, g, m->a, Mp, s)) return st;
-    g = GemmArgs{m->a, d, ly.wgu, d, M, 2 * m->f_pad, d, m->u, m->f_pad, nullptr, 1.0f};
-    g.w_packed = true;
+    g = GemmArgs{m->a, ly.wgu, W_BLOCKS, M, 2 * m->f_pad, d, m->u, 0, nullptr, 1.0f};
     if (cora_status st = gemm(m, EPI_SWIGLU, g, s, m->timing)) return st;
-    g = GemmArgs{m->u, m->f_pad, ly.wd, m->f_pad, M, d, m->f_pad, m->h, d, nullptr, 1.0f};
-    g.w_packed = true;
+    g = GemmArgs{m->u, ly.wd, W_BLOCKS, M, d, m->f_pad, m->h, d, nullptr, 1.0f};
     // the last layer's output is normalised only on the rows the LM head reads
     if (cora_status st = residual_gemm(m, g, l + 1 < n_layers ? m->a : nullptr, Mp, s))
       return st;
@@ -550,7 +546,7 @@ static cora_status run_layers(cora_model* m, const int32_t* tokens, int B, int L
 // few rows read the packed weights (HBM-bound stream), more rows take the tiled GEMM; the
 // choice is made for the planned row count (max_batch x rows per batch row)
 static bool lm_head_few_rows(const cora_model* m, int plan_out_rows) {
-  return m->lm_head_packed && plan_out_rows <= LM_HEAD_FUSED_MAX_ROWS &&
+  return plan_out_rows <= LM_HEAD_FUSED_MAX_ROWS &&
          lm_head_supported(plan_out_rows, m->cfg.vocab, m->cfg.d_model, m->cfg.d_model);
 }
 
@@ -567,15 +563,16 @@ static LmHeadArgs lm_args(const cora_model* m, int n_out_rows) {
 static cora_status lm_head(cora_model* m, const RowSel& sel, int n_out_rows, int plan_out_rows,
                            uint16_t* logits, hipStream_t s) {
   const auto& c = m->cfg;
-  HIP_TRY(launch_rmsnorm(m->h, m->ones, m->a, n_out_rows, c.d_model, c.rms_eps, sel, s));
-  if (lm_head_few_rows(m, plan_out_rows)) {
+  const bool few = lm_head_few_rows(m, plan_out_rows);
+  HIP_TRY(launch_rmsnorm(m->h, m->ones, m->a, n_out_rows, c.d_model, c.rms_eps, sel, !few, s));
+  if (few) {
     LmHeadArgs a = lm_args(m, n_out_rows);
     a.logits = logits;
     a.ldc = c.vocab;
     HIP_TRY(launch_lm_head(a, false, s));
     return CORA_OK;
   }
-  GemmArgs g{m->a, c.d_model, m->lm_head, c.d_model, n_out_rows, c.vocab, c.d_model, logits,
+  GemmArgs g{m->a, m->lm_head_packed, W_LM_HEAD, n_out_rows, c.vocab, c.d_model, logits,
              c.vocab, nullptr, c.logit_scale};
   return gemm(m, EPI_BF16, g, s);
 }
@@ -589,7 +586,7 @@ static cora_status score_rows(cora_model* m, const RowSel& sel, int B, int n_row
   const auto& c = m->cfg;
   const int M = B * n_rows, Mp = plan_rows(m, n_rows);
   if (lm_head_few_rows(m, Mp)) {
-    HIP_TRY(launch_rmsnorm(m->h, m->ones, m->a, M, c.d_model, c.rms_eps, sel, s));
+    HIP_TRY(launch_rmsnorm(m->h, m->ones, m->a, M, c.d_model, c.rms_eps, sel, false, s));
     const LmHeadArgs a = lm_args(m, M);
     HIP_TRY(launch_lm_head(a, true, s));
     HIP_TRY(launch_top1_merge(a, n_rows, vg.out_ld, vg.out_off, vg.top1, vg.conf, s));
@@ -603,8 +600,8 @@ static cora_status score_rows(cora_model* m, const RowSel& sel, int B, int n_row
   const int np = gemm_top1_parts(p, c.vocab);
   const size_t part_bytes = align_up((size_t)M * np * 4);
   if (3 * align_up((size_t)Mp * np * 4) <= (size_t)m->max_batch * m->max_rows * c.vocab * 2) {
-    HIP_TRY(launch_rmsnorm(m->h, m->ones, m->a, M, c.d_model, c.rms_eps, sel, s));
-    GemmArgs g{m->a, c.d_model, m->lm_head, c.d_model, M, c.vocab, c.d_model, nullptr, 0,
+    HIP_TRY(launch_rmsnorm(m->h, m->ones, m->a, M, c.d_model, c.rms_eps, sel, true, s));
+    GemmArgs g{m->a, m->lm_head_packed, W_LM_HEAD, M, c.vocab, c.d_model, nullptr, 0,
                nullptr, c.logit_scale};
     char* buf = reinterpret_cast<char*>(m->logits);
     g.part_m = reinterpret_cast<float*>(buf);
@@ -927,7 +924,7 @@ extern "C" cora_status cora_block_decode(cora_model* m, const int32_t* d_prompt,
 }
 
 // ---- weight read-back in logical [out, in] layout ---------------------------------------
-// Row-major host copy of a layer matrix stored in 64 x 64 blocks (physical rows x ld).
+// Row-major host copy of a layer matrix stored in 64 x 32 blocks (physical rows x ld).
 static cora_status read_packed(const uint16_t* d_packed, int64_t rows, int64_t ld,
                                std::vector<uint16_t>& out) {
   std::vector<uint16_t> p((size_t)(rows * ld));
@@ -935,8 +932,8 @@ static cora_status read_packed(const uint16_t* d_packed, int64_t rows, int64_t l
   out.resize(p.size());
   for (int64_t r = 0; r < rows; ++r)
     for (int64_t c = 0; c < ld; ++c)
-      out[(size_t)(r * ld + c)] = p[(size_t)(((r >> 6) * (ld >> 6) + (c >> 6)) * 4096 +
-                                             (r & 63) * 64 + (c & 63))];
+      out[(size_t)(r * ld + c)] = p[(size_t)(((r >> 6) * (ld >> 5) + (c >> 5)) * 2048 +
+                                             (r & 63) * 32 + (c & 31))];
   return CORA_OK;
 }
 
@@ -986,7 +983,7 @@ extern "C" cora_status cora_model_copy_tensor(cora_model* m, int32_t tensor_id, 
       std::vector<uint16_t> tmp;
       if (cora_status e = read_packed(ly.wgu, 2 * (int64_t)m->f_pad, d, tmp)) return e;
       for (int r = 0; r < F; ++r) {
-        const size_t pr = (size_t)(r >> 5) * 64 + (j == 5 ? 32 : 0) + (r & 31);
+        const size_t pr = (size_t)(r >> 4) * 32 + (j == 5 ? 16 : 0) + (r & 15);
         memcpy(out + (size_t)r * d, tmp.data() + pr * d, (size_t)d * 2);
       }
       return CORA_OK;

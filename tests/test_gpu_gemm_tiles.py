@@ -1,0 +1,53 @@
+"""GPU parity of the dense pass over the GEMM's tile configs and split counts.
+
+One-layer models whose row counts and widths make the plan pick every tile config, whole-K and
+split-K, with remainders in rows (a last tile of 1 to 130 rows), columns (ffn and head widths
+that are no multiple of the tile) and K (1 to 256 slices of 32), and batches whose sequences
+straddle the row tiles and the runs of 8 positions in which v is written.
+Oracle: oracle.forward in fp64; bound: the one of the other forward tests, 2e-2 x max |logit|.
+"""
+import numpy as np
+import pytest
+
+import seeded_inputs as si
+from oracle import forward as of
+from tests.gpu_common import log_case, require_gpu, to_dev
+from tests.parity import bf16_to_f32, logit_tolerance
+
+pytestmark = pytest.mark.gpu
+
+# (batch, length), d, heads, kv heads, head dim, ffn
+SHAPES = [
+    ((1, 1), 64, 1, 1, 64, 64),            # one row, one slice pair
+    ((1, 97), 512, 8, 2, 64, 688),         # 32 x 64 tiles; O split 2
+    ((2, 65), 1024, 8, 2, 128, 2816),      # O, down split 4
+    ((4, 65), 1024, 8, 2, 128, 2816),      # 64 x 64 and 64 x 128 tiles
+    ((13, 79), 512, 8, 8, 64, 4000),       # 256 x 192 gate/up, 128 x 64 QKV, odd rows
+    ((4, 500), 512, 4, 4, 128, 12288),     # 256 x 256 gate/up
+    ((4, 500), 512, 32, 32, 128, 4032),    # 256 x 128 QKV
+    ((1, 513), 2048, 4, 1, 64, 8192),      # one row past two 256-row tiles
+    ((3, 333), 2048, 16, 16, 128, 1100),   # 128 x 192 QKV
+    ((1, 65), 4096, 4, 2, 128, 1024),      # QKV split 8: partials and their finish kernel
+    ((4, 65), 8192, 4, 2, 128, 64),        # widest d, 256 slices
+    ((8, 375), 256, 16, 16, 128, 1200),    # many row tiles (more than one group of 8)
+    ((4, 575), 256, 32, 16, 64, 640),
+    ((6, 215), 1024, 32, 32, 128, 512),    # 256 x 192 / 256 x 256 QKV, 10 rows past a tile
+    ((3, 1000), 1024, 24, 24, 128, 512),
+]
+
+
+@pytest.mark.parametrize("bl,d,H,Hkv,hd,ffn", SHAPES, ids=lambda v: str(v).replace(" ", ""))
+def test_one_layer(bl, d, H, Hkv, hd, ffn):
+    require_gpu()
+    from paper_2608_11235_amd import Model
+    B, L = bl
+    spec = si.ModelSpec("tiles", 1, d, H, Hkv, hd, ffn, 500, 7, True, 1e-6, 1e6, 6.0)
+    log_case(f"tiles B={B} L={L} d={d} H={H}/{Hkv}x{hd} ffn={ffn}")
+    tokens = si.prompt_tokens(3, B, L, spec.vocab, spec.mask_id)
+    rows = np.unique(np.concatenate([np.arange(min(L, 12)), np.arange(max(0, L - 12), L)]))
+    with Model(spec, seed=1, max_batch=B, max_seq=L) as m:
+        got = bf16_to_f32(m.forward_logits(to_dev(tokens), 0, L).cpu().numpy())[:, rows]
+    ref = of.forward_logits(si.HostWeights(spec, 1), spec, tokens, rows)
+    err = np.abs(got.astype(np.float64) - ref)
+    print(f"max_err={err.max():.4g} tol={logit_tolerance(ref):.4g}")
+    assert err.max() <= logit_tolerance(ref)
