@@ -9,8 +9,10 @@
 //   A  [K / 32][M][32]: 16 rows of one panel are 1 KB
 //   W  (W_BLOCKS) 64 x 32 blocks, row-major inside, block (n / 64, k / 32) at
 //      ((n / 64) * K / 32 + k / 32) * 4 KB, N % 64 == 0; or (W_LM_HEAD) the LM head's packed
-//      layout (lm_head.hip), 1 KB blocks of 16 rows x 32 k, zero rows up to N's next multiple
-//      of 32.
+//      layout (lm_head.hip), 1 KB blocks of 16 rows x 32 k in the MFMA operand's lane order,
+//      zero rows up to N's next multiple of 32.  These blocks go to LDS and come back as they
+//      are: a load that gathers their 16-byte chunks into 64-byte rows touches four times the
+//      cache lines and runs at 38 GB/s a CU out of L2, a linear one at 131.
 // What bounds the loop is the rate of cache lines that a CU's loads touch: with row-major
 // operands (64 bytes of each of 16 rows, twice the lines) the same loop runs 18 % slower at
 // 4096 x 37888 x 3584, and 25 % slower at 256 x 128 tiles.
@@ -118,7 +120,11 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, OCC) void k_gemm(GemmArgs g)
   constexpr int ROWB = BK * 2, STAGE = (BM + BN) * ROWB;
   static_assert(ST % 2 == 1 && ST >= 3 && ST <= 9, "the tail pairs sections: an odd number of stages");
   static_assert(EPI != EPI_SWIGLU || TN % 2 == 0, "SwiGLU epilogue pairs 16-column blocks");
-  __shared__ __attribute__((aligned(1024))) uint16_t lds[ST * STAGE / 2];
+  // dynamic: a static array of more than half the CU's LDS would tell the compiler that one
+  // wavefront per SIMD is all there is, and it then spreads accumulators over AGPRs and moves
+  // them back and forth in the loop (128 x 192 as 4 wavefronts: 63 us, without moves 53 us)
+  extern __shared__ __attribute__((aligned(1024))) uint16_t lds[];
+  constexpr size_t LDS_BYTES = (size_t)ST * STAGE;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -154,8 +160,9 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, OCC) void k_gemm(GemmArgs g)
   }
 #pragma unroll
   for (int t = 0; t < LB; ++t) {
-    const int n = min(n0 + (t * NW + wave) % GB * 16 + lr, n_rows - 1) - (n0 & ~63), c = ls ^ swz(lr);
-    vob[t] = lm ? (n >> 5) * 64 * g.K + ((n >> 4) & 1) * 2048 + ((n & 15) + 16 * c) * 16
+    const int nb = n0 + (t * NW + wave) % GB * 16;  // n_rows is a multiple of 16
+    const int n = min(nb + (lm ? 0 : lr), n_rows - (lm ? 16 : 1)) - (n0 & ~63), c = ls ^ swz(lr);
+    vob[t] = lm ? (n >> 5) * 64 * g.K + ((n >> 4) & 1) * 2048 + lane * 16
                 : (n >> 6) * 128 * g.K + (n & 63) * 64 + c * 16;
   }
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
@@ -179,7 +186,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, OCC) void k_gemm(GemmArgs g)
   // fragments: lane holds row (lane % 16), k chunk (lane / 16) * 8
   const int fr = lane & 15, fc = lane >> 4;
   const int slot = (fc ^ swz(fr)) * 16;
-  const int ka = (wm * WR + fr) * ROWB + slot, kb = BM * ROWB + (wn * WC + fr) * ROWB + slot;
+  const int ka = (wm * WR + fr) * ROWB + slot, kb = BM * ROWB + wn * WC * ROWB + (lm ? lane * 16 : fr * ROWB + slot);
   const char* lp = reinterpret_cast<const char*>(lds);
   auto frag = [&](int off) { return as_bf16x8(*reinterpret_cast<const u32x4_t*>(lp + off)); };
   constexpr int NM = TM * TN;
@@ -283,7 +290,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, OCC) void k_gemm(GemmArgs g)
     constexpr int SPV = WR + 8;  // staged pitch, bf16
     constexpr int CPC = WR / 8;  // runs of 8 positions per head dimension
     constexpr int NCH = (16 * CPC + 63) / 64;
-    static_assert(sizeof(lds) >= (size_t)NW * 16 * SPV * 2, "stage");
+    static_assert(LDS_BYTES >= (size_t)NW * 16 * SPV * 2, "stage");
     __syncthreads();
     uint16_t* scr = lds + wave * 16 * SPV;
     // batch row and position of this lane's rows and of its runs: divided out once, not per
@@ -452,18 +459,23 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, OCC) void k_gemm(GemmArgs g)
 // X(cfg, WAVES_M, WAVES_N, TM, TN, stages, minimum waves per SIMD, workgroups per CU (LDS),
 //   slice_us, cu_us, tile_us): the last three are gemm_us's constants per 32-wide slice of a
 //   lone tile, per slice and resident tile on a busy chip, and per tile.
-// 0 to 4 serve the wide products (a larger tile moves fewer bytes per FLOP from L2 into LDS);
-// 5 to 8 products whose larger tiles would leave CUs idle: few rows, or few rows and columns.
-#define GEMM_CFGS(X)                                    \
-  X(0, 4, 2, 4, 8, 5, 1, 1, 0.507, 0.697, 5.53)   \
-  X(1, 8, 1, 2, 12, 5, 1, 1, 0.468, 0.555, 5.25)   \
-  X(2, 4, 2, 4, 4, 5, 1, 1, 0.342, 0.395, 3.08)   \
-  X(3, 4, 2, 2, 6, 5, 1, 1, 0.320, 0.344, 2.42)   \
-  X(4, 2, 2, 4, 4, 5, 2, 2, 0.236, 0.225, 2.33)   \
-  X(5, 2, 2, 4, 2, 5, 2, 2, 0.164, 0.176, 1.45)   \
-  X(6, 2, 2, 2, 4, 5, 2, 2, 0.181, 0.169, 1.41)   \
-  X(7, 2, 2, 2, 2, 7, 2, 2, 0.119, 0.106, 0.74)   \
-  X(8, 2, 2, 1, 2, 9, 2, 2, 0.095, 0.086, 0.66)
+// 0 to 4 and 9 serve the wide products (a larger tile moves fewer bytes per FLOP from L2 into
+// LDS); 5 to 8 products whose larger tiles would leave CUs idle: few rows, or few rows and
+// columns.  1, 3 and 9 hold their tile in wavefronts of 64 or 96 rows: the same tiles in
+// wavefronts of 32 rows read a third more bytes from LDS per MFMA (cold weights,
+// 512 x 24576 x 4096 at 256 x 192 91.6 -> 87.4 us, 512 x 12288 x 4096 at 128 x 192 57.8 ->
+// 53.2 us; 999 x 4608 x 3584 at 192 x 128 38.5 us, the others 42 and more).
+#define GEMM_CFGS(X)                              \
+  X(0, 4, 2, 4, 8, 5, 1, 1, 0.508, 0.626, 4.05)   \
+  X(1, 4, 2, 4, 6, 5, 2, 1, 0.439, 0.506, 3.42)   \
+  X(2, 4, 2, 4, 4, 5, 1, 1, 0.319, 0.357, 2.56)   \
+  X(3, 2, 2, 4, 6, 5, 2, 1, 0.286, 0.300, 2.55)   \
+  X(4, 2, 2, 4, 4, 5, 2, 2, 0.230, 0.217, 1.32)   \
+  X(5, 2, 2, 4, 2, 5, 2, 2, 0.187, 0.155, 0.41)   \
+  X(6, 2, 2, 2, 4, 5, 2, 2, 0.192, 0.161, 0.40)   \
+  X(7, 2, 2, 2, 2, 7, 2, 2, 0.113, 0.100, 0.52)   \
+  X(8, 2, 2, 1, 2, 9, 2, 2, 0.088, 0.078, 0.68)   \
+  X(9, 2, 2, 6, 4, 5, 2, 1, 0.250, 0.283, 2.39)
 struct CfgShape {
   int bm, bn, waves_n, per_cu;
   double slice_us, cu_us, tile_us;
@@ -478,7 +490,7 @@ static CfgShape cfg_shape(int cfg) {
   return {};
 }
 
-int gemm_num_cfgs() { return 9; }
+int gemm_num_cfgs() { return 10; }
 
 // wavefront columns per tile and their width (TN x 16) of each config
 int gemm_top1_parts(const GemmPlan& p, int N) {
@@ -489,11 +501,11 @@ int gemm_top1_parts(const GemmPlan& p, int N) {
 // Estimated time of one launch in microseconds: rounds of resident tiles, each the larger of
 // a tile's own latency per 32-wide slice and the chip's throughput with that many tiles
 // resident (a few busy CUs run faster than all: power), plus prologue and epilogue; the time
-// to stream the weights, of which two thirds overlap with it; plus the traffic of split-K partials and, in the
-// kernel downstream, of folding them (fold_us more where that kernel is an extra one).  The
-// constants are fitted to a sweep of all configs and split counts over 39 shapes (64 to 4096
-// rows, 256 to 152064 columns, K 256 to 18944); the plan it picks is on average within 1 % of
-// the fastest measured one.
+// to stream the weights, of which a little over half overlaps with it; plus the traffic of
+// split-K partials and, in the kernel downstream, of folding them (fold_us more where that
+// kernel is an extra one).  The constants are fitted to a sweep of all configs and split
+// counts over 47 shapes (64 to 4096 rows, 768 to 152064 columns, K 256 to 18944); the config
+// it picks is on average 0.3 %, at most 7 % slower than the fastest measured one.
 static double gemm_us(int M, int N, int K, int num_cus, int cfg, int splits, double fold_us) {
   const CfgShape sh = cfg_shape(cfg);
   const double nk = (double)K / BK / splits;
@@ -502,12 +514,12 @@ static double gemm_us(int M, int N, int K, int num_cus, int cfg, int splits, dou
   auto round_us = [&](int64_t n) {
     const double per_cu = (double)std::min<int64_t>(sh.per_cu, (n + num_cus - 1) / num_cus);
     const double busy = std::min(1.0, (double)n / num_cus);
-    return nk * std::max(sh.slice_us, per_cu * sh.cu_us * (0.41 + 0.59 * busy)) + sh.tile_us;
+    return nk * std::max(sh.slice_us, per_cu * sh.cu_us * (0.54 + 0.46 * busy)) + sh.tile_us;
   };
   double us = 1.4 + (double)(grid / slots) * round_us(slots);
   if (grid % slots) us += round_us(grid % slots);
-  const double stream_us = 1.4 + (double)N * K * 2 / 6.3e6;  // the weights at 6.3 TB/s
-  us = std::max(us, stream_us) + 0.37 * std::min(us, stream_us);
+  const double stream_us = 1.4 + (double)N * K * 2 / 7.3e6;  // the weights at 7.3 TB/s
+  us = std::max(us, stream_us) + 0.44 * std::min(us, stream_us);
   if (splits > 1) us += 0.37 * (double)splits * M * N * 4.0 / (1 << 20) + fold_us;
   return us;
 }
@@ -547,10 +559,12 @@ GemmPlan gemm_plan_split(int M, int N, int K, int num_cus, int splits, double fo
 // (hipExtLaunchKernel), so no marker packet sits between the events and the kernel.
 template <int WM, int WN, int TM, int TN, int ST, int OCC, int EPI>
 static hipError_t run(const GemmArgs& a, int grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  constexpr unsigned LDS = ST * (WM * TM + WN * TN) * 16 * BK * 2;  // ST stages of both operands
+  static_assert(LDS <= 160 * 1024, "LDS of a CU");
   if (e0 || e1)
-    hipExtLaunchKernelGGL((k_gemm<WM, WN, TM, TN, ST, OCC, EPI>), dim3(grid), dim3(WM * WN * 64), 0, s, e0, e1, 0, a);
+    hipExtLaunchKernelGGL((k_gemm<WM, WN, TM, TN, ST, OCC, EPI>), dim3(grid), dim3(WM * WN * 64), LDS, s, e0, e1, 0, a);
   else
-    hipLaunchKernelGGL((k_gemm<WM, WN, TM, TN, ST, OCC, EPI>), dim3(grid), dim3(WM * WN * 64), 0, s, a);
+    hipLaunchKernelGGL((k_gemm<WM, WN, TM, TN, ST, OCC, EPI>), dim3(grid), dim3(WM * WN * 64), LDS, s, a);
   return hipGetLastError();
 }
 

@@ -24,15 +24,16 @@ SHAPES = [
     ((4, 65), 1024, 8, 2, 128, 2816),      # 64 x 64 and 64 x 128 tiles
     ((13, 79), 512, 8, 8, 64, 4000),       # 256 x 192 gate/up, 128 x 64 QKV, odd rows
     ((4, 500), 512, 4, 4, 128, 12288),     # 256 x 256 gate/up
-    ((4, 500), 512, 32, 32, 128, 4032),    # 256 x 128 QKV
-    ((1, 513), 2048, 4, 1, 64, 8192),      # one row past two 256-row tiles
+    ((4, 500), 512, 32, 32, 128, 4032),    # 256 x 192 QKV
+    ((1, 513), 2048, 4, 1, 64, 8192),      # 192 x 128 gate/up and down (split 4)
     ((3, 333), 2048, 16, 16, 128, 1100),   # 128 x 192 QKV
     ((1, 65), 4096, 4, 2, 128, 1024),      # QKV split 8: partials and their finish kernel
     ((4, 65), 8192, 4, 2, 128, 64),        # widest d, 256 slices
     ((8, 375), 256, 16, 16, 128, 1200),    # many row tiles (more than one group of 8)
     ((4, 575), 256, 32, 16, 64, 640),
-    ((6, 215), 1024, 32, 32, 128, 512),    # 256 x 192 / 256 x 256 QKV, 10 rows past a tile
+    ((6, 215), 1024, 32, 32, 128, 512),    # 192 x 128 QKV and O, 138 rows in the last tile
     ((3, 1000), 1024, 24, 24, 128, 512),
+    ((1, 700), 512, 24, 24, 128, 128),     # 256 x 128 QKV, last tile of 188 rows
 ]
 
 
@@ -48,6 +49,27 @@ def test_one_layer(bl, d, H, Hkv, hd, ffn):
     with Model(spec, seed=1, max_batch=B, max_seq=L) as m:
         got = bf16_to_f32(m.forward_logits(to_dev(tokens), 0, L).cpu().numpy())[:, rows]
     ref = of.forward_logits(si.HostWeights(spec, 1), spec, tokens, rows)
+    err = np.abs(got.astype(np.float64) - ref)
+    print(f"max_err={err.max():.4g} tol={logit_tolerance(ref):.4g}")
+    assert err.max() <= logit_tolerance(ref)
+
+
+# rows and vocabularies (no multiples of 32, so the last weight group and tile are ragged) that
+# take the tiled LM head through each tile config
+HEADS = [(200, 50257), (500, 20011), (500, 9999), (300, 20011), (200, 5003), (130, 20011),
+         (130, 5003), (96, 5003), (65, 1001)]
+
+
+@pytest.mark.parametrize("rows,vocab", HEADS)
+def test_tiled_lm_head(rows, vocab):
+    require_gpu()
+    from paper_2608_11235_amd import Model
+    spec = si.ModelSpec("heads", 0, 256, 4, 4, 64, 64, vocab, 7, False, 1e-6, 1e4, 6.0)
+    log_case(f"tiled LM head rows={rows} vocab={vocab}")
+    tokens = si.prompt_tokens(3, 1, rows, spec.vocab, spec.mask_id)
+    with Model(spec, seed=1, max_batch=1, max_seq=rows) as m:
+        got = bf16_to_f32(m.forward_logits(to_dev(tokens), 0, rows).cpu().numpy())
+    ref = of.forward_logits(si.HostWeights(spec, 1), spec, tokens, np.arange(rows))
     err = np.abs(got.astype(np.float64) - ref)
     print(f"max_err={err.max():.4g} tol={logit_tolerance(ref):.4g}")
     assert err.max() <= logit_tolerance(ref)
