@@ -284,66 +284,82 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, OCC) void k_gemm(GemmArgs g)
     // section (q, k or v): section widths are multiples of 64.  v leaves transposed: the
     // block passes through this wavefront's part of LDS (free once every wavefront is past
     // its last slice) and is written as runs of 8 positions.
+    // The cos/sin loads of a block row are issued before the stores of the one before it: a
+    // load queued behind a store waits for that store too (loaded per block column, the
+    // epilogue was 20 to 30 us of 4096 x 4608 x 3584 and of 1280 x 12288 x 4096).
     const QkvOut& o = g.qkv;
-    const int hd = o.head_dim, half = hd / 2;
-    const int hq = o.n_heads * hd, hkv = o.n_kv_heads * hd;
+    const int hd = o.head_dim, hsh = 31 - __builtin_clz(hd);  // 64 or 128
+    const int hq = o.n_heads * hd, hqk = hq + o.n_kv_heads * hd;
     constexpr int SPV = WR + 8;  // staged pitch, bf16
     constexpr int CPC = WR / 8;  // runs of 8 positions per head dimension
     constexpr int NCH = (16 * CPC + 63) / 64;
     static_assert(LDS_BYTES >= (size_t)NW * 16 * SPV * 2, "stage");
+    const int c_wave = n0 + wn * WC;  // wave-uniform, like everything derived from it
+    if (g.bias) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        if (c_wave + j * 16 >= g.N) continue;
+        const f32x4_t bias = *reinterpret_cast<const f32x4_t*>(g.bias + c_wave + j * 16 + 4 * fc);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) acc[i][j] += bias;
+      }
+    }
+    if (c_wave < hqk) {
+      // batch row and position of this lane's rows: divided out once, not per block column
+      int rp[TM];
+      int64_t oq[TM], ok[TM];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        const int m = min(row0 + i * 16, g.M - 1), rb = m / o.L;
+        rp[i] = m - rb * o.L;
+        oq[i] = ((int64_t)rb * o.n_heads * o.Ls + rp[i]) * hd + 4 * fc;
+        ok[i] = ((int64_t)rb * o.n_kv_heads * o.Ls + rp[i]) * hd + 4 * fc;
+      }
+      f32x4_t tab[2][TN];  // (cos, sin) of this lane's two pairs
+      auto load_tab = [&](int i, f32x4_t(&t)[TN]) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          t[j] = *reinterpret_cast<const f32x4_t*>(o.cs_t + rp[i] * hd + ((c_wave + j * 16) & (hd - 1)) + 4 * fc);
+      };
+      load_tab(0, tab[0]);
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        if (i + 1 < TM) load_tab(i + 1, tab[(i + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+        const bool in = row0 + i * 16 < g.M;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          const int c0 = c_wave + j * 16;
+          if (c0 >= hqk || !in) continue;
+          const int cc0 = c0 < hq ? c0 : c0 - hq;
+          uint16_t* base = (c0 < hq ? o.q : o.k) + (int64_t)(cc0 >> hsh) * o.Ls * hd + (cc0 & (hd - 1));
+          const f32x4_t x = acc[i][j], t = tab[i & 1][j];
+          *reinterpret_cast<u32x2_t*>(base + (c0 < hq ? oq[i] : ok[i])) =
+              u32x2_t{pack_bf16x2(x[0] * t[0] - x[1] * t[1], x[1] * t[0] + x[0] * t[1]),
+                      pack_bf16x2(x[2] * t[2] - x[3] * t[3], x[3] * t[2] + x[2] * t[3])};
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
     __syncthreads();
-    uint16_t* scr = lds + wave * 16 * SPV;
-    // batch row and position of this lane's rows and of its runs: divided out once, not per
-    // block column
-    int rb[TM], rp[TM], vb[NCH], vp[NCH];
+    if (c_wave + WC > hqk) {
+      uint16_t* scr = lds + wave * 16 * SPV;
+      int vb[NCH], vp[NCH];  // batch row and position of this lane's runs
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const int m = min(row0 + i * 16, g.M - 1);
-      rb[i] = m / o.L;
-      rp[i] = m - rb[i] * o.L;
-    }
+      for (int k = 0; k < NCH; ++k) {
+        const int m = m0 + wm * WR + (lane + 64 * k) % CPC * 8;
+        vb[k] = m / o.L;
+        vp[k] = m - vb[k] * o.L;
+      }
 #pragma unroll
-    for (int k = 0; k < NCH; ++k) {
-      const int m = m0 + wm * WR + (lane + 64 * k) % CPC * 8;
-      vb[k] = m / o.L;
-      vp[k] = m - vb[k] * o.L;
-    }
+      for (int j = 0; j < TN; ++j) {
+        const int c0 = c_wave + j * 16;
+        if (c0 < hqk || c0 >= g.N) continue;
+        const int head = (c0 - hqk) >> hsh, d0 = (c0 - hqk) & (hd - 1);
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int c0 = n0 + wn * WC + j * 16;  // wave-uniform
-      if (c0 >= g.N) continue;
-      const int sec = c0 < hq ? 0 : (c0 < hq + hkv ? 1 : 2);
-      const int cc0 = c0 - (sec == 0 ? 0 : (sec == 1 ? hq : hq + hkv));
-      const int head = cc0 / hd, d0 = cc0 % hd;
-      const float4 bias = g.bias ? *reinterpret_cast<const float4*>(g.bias + c0 + 4 * fc) : float4{0.f, 0.f, 0.f, 0.f};
-      if (sec < 2) {
-        uint16_t* base = sec == 0 ? o.q : o.k;
-        const int nh = sec == 0 ? o.n_heads : o.n_kv_heads, pd = d0 + 4 * fc;
-        // the cos/sin loads of a block column are issued before its first store (a load
-        // queued behind a store waits for it too)
-        float2 cs[TM], sn[TM];
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          cs[i] = *reinterpret_cast<const float2*>(o.cos_t + rp[i] * half + (pd >> 1));
-          sn[i] = *reinterpret_cast<const float2*>(o.sin_t + rp[i] * half + (pd >> 1));
-        }
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          if (row0 + i * 16 >= g.M) continue;
-          const float x0 = acc[i][j][0] + bias.x, x1 = acc[i][j][1] + bias.y;
-          const float x2 = acc[i][j][2] + bias.z, x3 = acc[i][j][3] + bias.w;
-          u32x2_t p;
-          p.x = pack_bf16x2(x0 * cs[i].x - x1 * sn[i].x, x1 * cs[i].x + x0 * sn[i].x);
-          p.y = pack_bf16x2(x2 * cs[i].y - x3 * sn[i].y, x3 * cs[i].y + x2 * sn[i].y);
-          *reinterpret_cast<u32x2_t*>(base + ((int64_t)(rb[i] * nh + head) * o.Ls + rp[i]) * hd + pd) = p;
-        }
-      } else {
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          const float x[4] = {acc[i][j][0] + bias.x, acc[i][j][1] + bias.y, acc[i][j][2] + bias.z, acc[i][j][3] + bias.w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) scr[(4 * fc + e) * SPV + i * 16 + fr] = (uint16_t)f32_to_bf16_bits(x[e]);
-        }
+          for (int e = 0; e < 4; ++e) scr[(4 * fc + e) * SPV + i * 16 + fr] = (uint16_t)f32_to_bf16_bits(acc[i][j][e]);
 #pragma unroll
         for (int k = 0; k < NCH; ++k) {
           const int id = lane + 64 * k, dcol = id / CPC, rr = id % CPC * 8;
@@ -409,20 +425,34 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, OCC) void k_gemm(GemmArgs g)
     // N % 4 == 0 (checked at launch): a lane's 4 columns are in or out together
     float* C = reinterpret_cast<float*>(g.C) +
                (EPI == EPI_PART_F32 ? (int64_t)split * g.M * g.ldc : (int64_t)0);
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const int row = row0 + i * 16;
-      if (row >= g.M) continue;
-      float* dst = C + (int64_t)row * g.ldc + col0;
-      if constexpr (EPI == EPI_ADD_F32) {
-        f32x4_t h[TN];
+    if constexpr (EPI == EPI_ADD_F32) {
+      // the next block row's loads go out before this one's stores (see EPI_QKV_ROPE)
+      f32x4_t h[2][TN];
+      auto load_h = [&](int i, f32x4_t(&v)[TN]) {
+        if (row0 + i * 16 >= g.M) return;
 #pragma unroll
         for (int j = 0; j < TN; ++j)
-          if (col0 + j * 16 < g.N) h[j] = *reinterpret_cast<const f32x4_t*>(dst + j * 16);
+          if (col0 + j * 16 < g.N) v[j] = *reinterpret_cast<const f32x4_t*>(C + (int64_t)(row0 + i * 16) * g.ldc + col0 + j * 16);
+      };
+      load_h(0, h[0]);
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-          if (col0 + j * 16 < g.N) *reinterpret_cast<f32x4_t*>(dst + j * 16) = h[j] + acc[i][j];
-      } else {
+      for (int i = 0; i < TM; ++i) {
+        if (i + 1 < TM) load_h(i + 1, h[(i + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (row0 + i * 16 < g.M) {
+          float* dst = C + (int64_t)(row0 + i * 16) * g.ldc + col0;
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            if (col0 + j * 16 < g.N) *reinterpret_cast<f32x4_t*>(dst + j * 16) = h[i & 1][j] + acc[i][j];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        const int row = row0 + i * 16;
+        if (row >= g.M) continue;
+        float* dst = C + (int64_t)row * g.ldc + col0;
 #pragma unroll
         for (int j = 0; j < TN; ++j)
           if (col0 + j * 16 < g.N) *reinterpret_cast<f32x4_t*>(dst + j * 16) = acc[i][j];

@@ -76,7 +76,7 @@ enum GemmEpi {
 // k [B, Hkv, Ls, hd] in the interleaved dim order and v transposed vt [B, Hkv, hd, Ls].
 struct QkvOut {
   uint16_t *q, *k, *vt;
-  const float *cos_t, *sin_t;  // [Ls, hd/2]
+  const float* cs_t;  // [Ls, hd/2] pairs (cos, sin)
   int L, Ls, n_heads, n_kv_heads, head_dim;
 };
 struct GemmArgs {

@@ -117,7 +117,7 @@ __global__ __launch_bounds__(256) void k_qkv_finish(const float* __restrict__ pa
   const int r0 = blockIdx.y * 4;
   const int nr = M - r0 < 4 ? M - r0 : 4;
   const int64_t slab = (int64_t)M * N;
-  const int hd = o.head_dim, half = hd / 2;
+  const int hd = o.head_dim;
   const int hq = o.n_heads * hd, hkv = o.n_kv_heads * hd;
   const int sec = c < hq ? 0 : (c < hq + hkv ? 1 : 2);
   const int cc = c - (sec == 0 ? 0 : (sec == 1 ? hq : hq + hkv));
@@ -164,14 +164,13 @@ __global__ __launch_bounds__(256) void k_qkv_finish(const float* __restrict__ pa
     // every row's cos/sin loads are issued before the first store: a load behind a store
     // would wait for that store too
     int bt[4], pt[4];
-    float2 cs[4], sn[4];
+    f32x4_t cs[4];  // (cos, sin) of both pairs
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       bt[t] = b;
       pt[t] = pos;
       if (t < nr) {
-        cs[t] = *reinterpret_cast<const float2*>(o.cos_t + pos * half + (pd >> 1));
-        sn[t] = *reinterpret_cast<const float2*>(o.sin_t + pos * half + (pd >> 1));
+        cs[t] = *reinterpret_cast<const f32x4_t*>(o.cs_t + pos * hd + pd);
       }
       if (++pos == o.L) {
         pos = 0;
@@ -182,8 +181,8 @@ __global__ __launch_bounds__(256) void k_qkv_finish(const float* __restrict__ pa
     for (int t = 0; t < 4; ++t) {
       if (t >= nr) break;
       u32x2_t q;
-      q.x = pack_bf16x2(x[t][0] * cs[t].x - x[t][1] * sn[t].x, x[t][1] * cs[t].x + x[t][0] * sn[t].x);
-      q.y = pack_bf16x2(x[t][2] * cs[t].y - x[t][3] * sn[t].y, x[t][3] * cs[t].y + x[t][2] * sn[t].y);
+      q.x = pack_bf16x2(x[t][0] * cs[t][0] - x[t][1] * cs[t][1], x[t][1] * cs[t][0] + x[t][0] * cs[t][1]);
+      q.y = pack_bf16x2(x[t][2] * cs[t][2] - x[t][3] * cs[t][3], x[t][3] * cs[t][2] + x[t][2] * cs[t][3]);
       uint16_t* dst = sec == 0 ? o.q + ((int64_t)(bt[t] * o.n_heads + head) * o.Ls + pt[t]) * hd
                                : o.k + ((int64_t)(bt[t] * o.n_kv_heads + head) * o.Ls + pt[t]) * hd;
       *reinterpret_cast<u32x2_t*>(dst + pd) = q;

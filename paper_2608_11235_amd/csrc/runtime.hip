@@ -98,7 +98,7 @@ struct cora_model {
   float* h = nullptr;
   uint16_t *a = nullptr, *q = nullptr, *k = nullptr, *vt = nullptr;
   uint16_t *attn = nullptr, *u = nullptr, *logits = nullptr;
-  float *rope_cos = nullptr, *rope_sin = nullptr;
+  float* rope_cs = nullptr;  // (cos, sin) pairs
   int num_cus = 256;
   float* splitk_ws = nullptr;
   size_t splitk_ws_floats = 0;
@@ -238,7 +238,7 @@ extern "C" cora_status cora_model_create(const cora_model_cfg* cfg, uint64_t see
   size_t wsb = 3 * align_up(lmh_parts * 4) + align_up(skw * 4) + align_up(M * d * 4) + align_up(M * (size_t)(d > m->hq ? d : m->hq) * 2) +
                align_up(Ms * m->hq * 2) + 2 * align_up(Ms * m->hkv * 2) +
                align_up(M * m->hq * 2) + align_up(M * m->f_pad * 2) + align_up(rows * V * 2) +
-               2 * align_up((size_t)m->max_seq_pad * (hd / 2) * 4) +
+               align_up((size_t)m->max_seq_pad * hd * 4) +
                // decode state
                align_up(BL * 4) * 3 + align_up(BL) + align_up(max_batch * 4) * 3 +
                align_up(BL * 4) * 2 + align_up(rows) + align_up((size_t)max_batch * max_seq * 4) +
@@ -285,8 +285,7 @@ extern "C" cora_status cora_model_create(const cora_model_cfg* cfg, uint64_t see
   m->attn = a.take<uint16_t>(M * m->hq);
   m->u = a.take<uint16_t>(M * m->f_pad);
   m->logits = a.take<uint16_t>(rows * V);
-  m->rope_cos = a.take<float>((size_t)m->max_seq_pad * (hd / 2));
-  m->rope_sin = a.take<float>((size_t)m->max_seq_pad * (hd / 2));
+  m->rope_cs = a.take<float>((size_t)m->max_seq_pad * hd);
   m->s_tokens = a.take<int32_t>(BL);
   m->s_prev = a.take<int32_t>(BL);
   m->s_persist = a.take<int32_t>(BL);
@@ -345,15 +344,14 @@ extern "C" cora_status cora_model_create(const cora_model_cfg* cfg, uint64_t see
     }
     // RoPE tables in fp64, stored fp32: angle = pos * theta^(-2j/hd)
     const int half = hd / 2;
-    std::vector<float> cs((size_t)m->max_seq_pad * half), sn(cs.size());
+    std::vector<float> cs((size_t)m->max_seq_pad * hd);
     for (int p = 0; p < m->max_seq_pad; ++p)
       for (int j = 0; j < half; ++j) {
         const double ang = (double)p * pow((double)cfg->rope_theta, -2.0 * j / hd);
-        cs[(size_t)p * half + j] = (float)cos(ang);
-        sn[(size_t)p * half + j] = (float)sin(ang);
+        cs[(size_t)p * hd + 2 * j] = (float)cos(ang);
+        cs[(size_t)p * hd + 2 * j + 1] = (float)sin(ang);
       }
-    HIP_TRY(hipMemcpyAsync(m->rope_cos, cs.data(), cs.size() * 4, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(m->rope_sin, sn.data(), sn.size() * 4, hipMemcpyHostToDevice, s));
+    HIP_TRY(hipMemcpyAsync(m->rope_cs, cs.data(), cs.size() * 4, hipMemcpyHostToDevice, s));
     HIP_TRY(hipStreamSynchronize(s));
     return CORA_OK;
   }();
@@ -526,7 +524,7 @@ static cora_status run_layers(cora_model* m, const int32_t* tokens, int B, int L
     const auto& ly = m->layers[l];
     // m->a holds rmsnorm(h) of this layer's input
     GemmArgs g{m->a, ly.wqkv, W_BLOCKS, M, m->qkv_n, d, nullptr, 0, ly.bqkv, 1.0f};
-    g.qkv = QkvOut{m->q, m->k, m->vt, m->rope_cos, m->rope_sin, L, Ls, c.n_heads, c.n_kv_heads,
+    g.qkv = QkvOut{m->q, m->k, m->vt, m->rope_cs, L, Ls, c.n_heads, c.n_kv_heads,
                    c.head_dim};
     if (cora_status st = qkv_gemm(m, g, Mp, s)) return st;
     HIP_TRY(launch_attention(m->q, m->k, m->vt, m->attn, B, L, Ls, c.n_heads, c.n_kv_heads,
