@@ -21,8 +21,9 @@ __host__ __device__ inline int rope_pair_pos(int j, int hd) { return j < hd / 2 
 hipError_t launch_fill_f32(float* dst, float v, int64_t n, hipStream_t s);
 
 // ---- elementwise ------------------------------------------------------------------------
-hipError_t launch_embed(const int32_t* tokens, const uint16_t* E, float* h, int M, int d, int V,
-                        hipStream_t s);
+// h[m] = E[tokens[m]] and, when norm_out is not null, norm_out = bf16(rmsnorm(h) * w) in K panels
+hipError_t launch_embed(const int32_t* tokens, const uint16_t* E, float* h, int rows, int d, int V,
+                        const float* w, uint16_t* norm_out, float eps, hipStream_t s);
 // out[j] = rmsnorm(h[src(j)]) with src(j) = j (mode 0), or for j = b * n_rows + r:
 // b * L + row_begin + r (mode 1), b * L + lo_b + r with lo_b the active block start (mode 2).
 struct RowSel {
@@ -30,7 +31,7 @@ struct RowSel {
   const int32_t* block_idx;
 };
 // The output is row-major, or K panels [d / 32][rows][32] (the GEMMs' A operand, d % 32 == 0)
-// when panels is set.
+// when panels is set.  d % 32 == 0 and d <= RESIDUAL_NORM_MAX_D.
 hipError_t launch_rmsnorm(const float* h, const float* w, uint16_t* out, int rows, int d,
                           float eps, RowSel sel, bool panels, hipStream_t s);
 // h[r, :] += part[0][r, :] + ... + part[splits-1][r, :] (partials [splits][rows][d], summed in

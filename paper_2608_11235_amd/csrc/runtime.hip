@@ -516,10 +516,9 @@ static cora_status residual_gemm(cora_model* m, GemmArgs g, uint16_t* norm_out, 
 static cora_status run_layers(cora_model* m, const int32_t* tokens, int B, int L, hipStream_t s) {
   const auto& c = m->cfg;
   const int d = c.d_model, M = B * L, Ls = round_up(L, 64), Mp = plan_rows(m, L);
-  HIP_TRY(launch_embed(tokens, m->embed, m->h, M, d, c.vocab, s));
-  const RowSel all{0, L, 0, 0, 0, 0, 0, nullptr};
-  HIP_TRY(launch_rmsnorm(m->h, m->ones, m->a, M, d, c.rms_eps, all, true, s));
   const size_t n_layers = m->layers.size();
+  HIP_TRY(launch_embed(tokens, m->embed, m->h, M, d, c.vocab, m->ones, n_layers ? m->a : nullptr,
+                       c.rms_eps, s));
   for (size_t l = 0; l < n_layers; ++l) {
     const auto& ly = m->layers[l];
     // m->a holds rmsnorm(h) of this layer's input
