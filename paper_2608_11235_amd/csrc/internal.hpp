@@ -177,10 +177,10 @@ hipError_t launch_vocab_top1(const VocabGateArgs& a, hipStream_t s);
 // memory, fully overwritten) and are folded in vocab order by k_top1_merge.  top1 agrees
 // with launch_vocab_top1 bit for bit; conf differs only in the fp32 summation order.
 struct VocabSplit {
-  int parts, chunks;  // chunks: set by the launcher (16-byte chunks, or entries, per part)
+  int parts, chunk;  // chunk: entries per part (a multiple of 8), set by the launcher
   float* pm; float* ps; int* pa;
 };
-// parts for `rows` rows: ~4 workgroups per CU, each part >= 1024 chunks, rows * parts <=
+// parts for `rows` rows: ~4 workgroups per CU, each part >= 8192 entries, rows * parts <=
 // max_partials; 0 when even one part per row does not fit
 int vocab_split_parts(int rows, int V, int num_cus, int64_t max_partials);
 hipError_t launch_vocab_top1_split(const VocabGateArgs& a, const VocabSplit& sp, hipStream_t s);

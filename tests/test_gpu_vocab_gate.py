@@ -32,8 +32,10 @@ def _oracle(w, k, delta_p, m_req, gate_on, row_begin, scope="block", eos_id=None
     return st, outs
 
 
-def _gpu(w, k, delta_p, m_req, gate_on, row_begin, scope="block", eos_id=None):
-    from paper_2608_11235_amd import DecodeState, Gate, Sched, vocab_gate
+def _gpu(w, k, delta_p, m_req, gate_on, row_begin, scope="block", eos_id=None, entry="vocab_gate"):
+    import paper_2608_11235_amd as pkg
+    from paper_2608_11235_amd import DecodeState, Gate, Sched
+    vocab_gate = getattr(pkg, entry)
     B, R, V = w.logits_bits.shape
     L = w.state["tokens"].shape[1]
     st = DecodeState.from_host(w.state, w.prompt_len, L - w.prompt_len, R, w.block_len)
@@ -166,6 +168,26 @@ def test_vocab_gate_odd_vocab_and_k(V):
     for k in (0, 3, 16, -1):
         ex, _ = _check(w, k, 0.3, 1, True)
         assert ex <= 1
+
+
+@pytest.mark.parametrize("B", [1, 5])
+@pytest.mark.parametrize("V", [9, 4099, 16384, 16389, 40003])  # rows start at any multiple of 2 bytes
+def test_vocab_gate_row_alignment(V, B):
+    """Mask ids and maxima before the first 16-byte boundary of a row, in its chunks and after the
+    last whole one, through both entry points."""
+    require_gpu()
+    for mask_id in (0, V // 2, V - 1):
+        log_case(f"vocab_gate alignment V={V} B={B} mask={mask_id}")
+        w = si.vocab_gate_workload(seed=V + mask_id, batch=B, prompt_len=16, gen_len=64, vocab=V,
+                                   mask_id=mask_id, block_len=32, steps_per_block=32,
+                                   masked_in_block=4, spike_max=9.0)
+        bits = w.logits_bits
+        for r in range(bits.shape[1]):                     # the row's maximum at either end
+            if r % 3 < 2:
+                bits[:, r, [0, V - 1][r % 3]] = 0x4180     # 16.0
+        st_or, outs = _oracle(w, 1, 0.3, 1, True, 0)
+        for entry in ("vocab_gate", "vocab_gate_noalloc"):
+            _compare(w, _gpu(w, 1, 0.3, 1, True, 0, entry=entry), st_or, outs, 1, 0.3, True, 0)
 
 
 def test_vocab_gate_ties_lowest_id():

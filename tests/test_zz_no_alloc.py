@@ -78,7 +78,7 @@ def test_noalloc_matches_vocab_gate():
     w = si.vocab_gate_workload(seed=9, batch=1)
     lo = w.prompt_len + int(w.state["block_idx"][0]) * w.block_len
     u2 = _case(w, w.logits_bits[:, lo:lo + w.block_len], -1, -1, Gate(0.05, 1, True))
-    # 3: smaller still: odd vocabulary (element loop), 2 x 32 block rows
+    # 3: smaller still: odd vocabulary (rows start unaligned), 2 x 32 block rows
     log_case("noalloc call 3: B=2 x 32 block rows, V=50001")
     w = si.vocab_gate_workload(seed=5, batch=2, prompt_len=16, gen_len=64, vocab=50001,
                                mask_id=25000)
