@@ -506,7 +506,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, OCC) void k_gemm(GemmArgs g)
 #define GEMM_CFGS(X)                              \
   X(0, 4, 2, 4, 8, 5, 1, 1, 0.508, 0.626, 4.05)   \
   X(1, 4, 2, 4, 6, 5, 2, 1, 0.439, 0.506, 3.42)   \
-  X(2, 4, 2, 4, 4, 5, 1, 1, 0.319, 0.357, 2.56)   \
+  X(2, 4, 2, 4, 4, 5, 1, 1, 0.319, 0.363, 2.56)   \
   X(3, 2, 2, 4, 6, 5, 2, 1, 0.286, 0.300, 2.55)   \
   X(4, 2, 2, 4, 4, 5, 2, 2, 0.230, 0.217, 1.32)   \
   X(5, 2, 2, 4, 2, 5, 2, 2, 0.187, 0.155, 0.41)   \
