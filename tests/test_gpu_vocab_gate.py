@@ -190,6 +190,61 @@ def test_vocab_gate_row_alignment(V, B):
             _compare(w, _gpu(w, 1, 0.3, 1, True, 0, entry=entry), st_or, outs, 1, 0.3, True, 0)
 
 
+# a tokenizer's banned ids carry one large negative value: -65536, -1e10, -1e30 or bf16's lowest
+@pytest.mark.parametrize("fill", [0xC780, 0xD015, 0xF14A, 0xFF7F], ids=hex)
+@pytest.mark.parametrize("V", [4096, 4099, 50257])
+def test_vocab_gate_filled_logits(V, fill):
+    """Rows of which all but 1 to 40 logits are one large negative number, one row of nothing else,
+    and rows whose maximum is bf16's largest number (alone, and as one of two): every sum holds
+    exp(0) = 1 of its maximum, so the confidence is finite and within CONF_RTOL, and the step
+    commits what the oracle does."""
+    require_gpu()
+    log_case(f"vocab_gate filled V={V} fill={fill:#x}")
+    w = si.vocab_gate_workload(seed=V, batch=2, prompt_len=8, gen_len=32, vocab=V, mask_id=V // 3,
+                               block_len=32, steps_per_block=32, masked_in_block=20, spike_max=6.0)
+    rng = np.random.default_rng(V)
+    bits = w.logits_bits
+    for b in range(bits.shape[0]):
+        for r in range(bits.shape[1]):
+            live = rng.choice(V, size=1 + (7 * r) % 40, replace=False)
+            keep = bits[b, r, live].copy()
+            if r % 5 < 4:
+                bits[b, r] = fill
+                bits[b, r, live] = keep
+            if r % 7 == 3:
+                bits[b, r, live[:1 + r % 2]] = 0x7F7F
+        bits[b, 12] = fill
+    st_or, outs = _oracle(w, 2, 0.3, 1, True, 0)
+    for entry in ("vocab_gate", "vocab_gate_noalloc"):
+        _compare(w, _gpu(w, 2, 0.3, 1, True, 0, entry=entry), st_or, outs, 2, 0.3, True, 0)
+
+
+@pytest.mark.parametrize("top", [0x4481, 0x457F, 0x4600, 0x467F, 0x4680, 0x4681, 0x4F00, 0xC600,
+                                 0xC67F, 0xC680, 0xC681], ids=hex)
+def test_vocab_gate_large_maxima(top):
+    """Maxima from 2^10 to 2^31 of either sign, on both sides of 2^14, where the exponent takes
+    another form; the logits below them are the next bf16 numbers down (8 to 64 lower, so at 2^12
+    hundreds of them still count) or ordinary ones."""
+    require_gpu()
+    V = 4099
+    log_case(f"vocab_gate large maxima top={top:#x}")
+    w = si.vocab_gate_workload(seed=top, batch=2, prompt_len=8, gen_len=32, vocab=V, mask_id=5,
+                               block_len=32, steps_per_block=32, masked_in_block=20, spike_max=6.0)
+    rng = np.random.default_rng(top)
+    down = 1 if top & 0x8000 else -1                       # bits of the next number down
+    bits = w.logits_bits
+    for r in range(bits.shape[1]):
+        at = rng.permutation(V)
+        if top & 0x8000:
+            bits[:, r] = 0xFF7F
+        bits[:, r, at[:300 * (r % 13)]] = top + down
+        bits[:, r, at[:200 * (r % 7)]] = top + 2 * down
+        bits[:, r, at[-1 - r % 3:]] = top
+    st_or, outs = _oracle(w, 2, 0.3, 1, True, 0)
+    for entry in ("vocab_gate", "vocab_gate_noalloc"):
+        _compare(w, _gpu(w, 2, 0.3, 1, True, 0, entry=entry), st_or, outs, 2, 0.3, True, 0)
+
+
 def test_vocab_gate_ties_lowest_id():
     """Exact bf16 ties for the maximum resolve to the lowest token id; the mask id is skipped."""
     require_gpu()
