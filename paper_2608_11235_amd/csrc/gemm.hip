@@ -415,9 +415,10 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, OCC) void k_gemm(GemmArgs g)
       }
       float s = 0.f;
       if (m != -INFINITY) {
-        const float ml = m * LOG2E;
+        const ExpBelow ex(m);
 #pragma unroll
-        for (int k = 0; k < TN * 4; ++k) s += fast_exp2(fmaf(v[k], LOG2E, -ml));
+        for (int k = 0; k < TN * 4; ++k) s += ex(v[k]);
+        s = ex.sum(s);
       }
       s += __shfl_xor(s, 16, 64);
       s += __shfl_xor(s, 32, 64);

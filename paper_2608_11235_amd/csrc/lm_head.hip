@@ -225,9 +225,10 @@ __global__ __launch_bounds__(256) void k_lm_head(LmHeadArgs a) {
       }
       float s = 0.f;
       if (m != -INFINITY) {
-        const float ml = m * LOG2E;
+        const ExpBelow ex(m);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) s += fast_exp2(fmaf(v8[i], LOG2E, -ml));
+        for (int i = 0; i < 8; ++i) s += ex(v8[i]);
+        s = ex.sum(s);
       }
       s += __shfl_xor(s, 16, 64);
       s += __shfl_xor(s, 32, 64);

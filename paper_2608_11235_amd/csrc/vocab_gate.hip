@@ -66,24 +66,14 @@ __device__ __forceinline__ void consume32(TopState& t, BestChunk& best, const fl
     t.arg = c + 256 * i;
   }
   if (t.m == -INFINITY) return;
-  // exp(v - m) as one fma per logit, 2^(v k + o).  Below |m| = 2^14: k = log2 e, o = -m k
-  // rounded; the rounding scales every term alike, by 2^(m k + o), which is taken back from the
-  // sum (to first order: what is left is at most 2.3e-7, and 1e-9 below |m| = 2^10).  From 2^14
-  // on that error would grow with |m| (inf or 0 at 4e9, inf - inf at bf16's lowest number, a
-  // usual fill of banned tokens), but two different bf16 numbers are 64 or more apart, so that a
-  // term is 1 where v == m and nothing a sum can notice elsewhere: k = 1, o = -m, exact.
-  // (v - m) * log2 e for every m is one operation more a logit: 8 x 512 x 126464 in 159.3 us
-  // against 157.8, 1024 x 100000 in 38.5 against 37.8.
-  const bool far = fabsf(t.m) >= 16384.f;
-  const float k = far ? 1.f : LOG2E, o = -(t.m * k);
+  const ExpBelow ex(t.m);
   float acc0 = 0.f, acc1 = 0.f;
 #pragma unroll
   for (int j = 0; j < 32; j += 2) {
-    acc0 += fast_exp2(fmaf(v[j], k, o));
-    acc1 += fast_exp2(fmaf(v[j + 1], k, o));
+    acc0 += ex(v[j]);
+    acc1 += ex(v[j + 1]);
   }
-  const float acc = acc0 + acc1, d = fmaf(t.m, k, o) * -0.69314718f;
-  t.s += fmaf(acc, d, acc);
+  t.s += ex.sum(acc0 + acc1);
 }
 
 // The lane is counted where it is needed, so that no register holds it through the loop: five

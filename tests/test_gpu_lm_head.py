@@ -12,6 +12,8 @@ GEMM's top-1 epilogue.  Two properties tie the paths together at any size:
 
 Logit parity with the oracle for both paths is in test_gpu_weights_forward.py.
 """
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -72,6 +74,14 @@ def test_fused_scores_match_own_logits(spec, B, blk):
     assert (out["top1"] == top).all(), f"{(out['top1'] != top).sum()} top-1 mismatches"
     rel = np.abs(out["conf"].astype(np.float64) - conf) / conf
     assert rel.max() <= 2e-5, f"confidence rel err {rel.max():.3g}"
+
+
+@pytest.mark.parametrize("scale", [2e4, 1e12, 1e37])
+@pytest.mark.parametrize("B", [1, 3])
+def test_fused_scores_large_logits(B, scale):
+    """Logit scales that put the maxima at 2e4 and far beyond: every sum holds exp(0) = 1 of its
+    maximum.  B = 1: the packed-weight stream; B = 3 (96 rows): the tiled GEMM's epilogue."""
+    test_fused_scores_match_own_logits(dataclasses.replace(RAGGED, logit_scale=scale), B, BLK)
 
 
 @pytest.mark.parametrize("spec,B,n_rows", [(RAGGED, 1, 20), (RAGGED, 2, 32), (si.TINY, 1, 32),
