@@ -146,10 +146,9 @@ typedef struct cora_model cora_model;
  * with mix the SplitMix64 finaliser and G = 0x9E3779B97F4A7C15.  Tensor ids:
  * 1 embedding [V, d], 2 LM head [V, d], and 100 + 16 l + j for layer l with
  * j = 0 wq, 1 wk, 2 wv, 3 wo, 4 wg, 5 wu, 6 wd, 7 bq, 8 bk, 9 bv.  Norm
- * weights are 1.  The LM head is also kept in a second, packed layout (the
- * order in which the few-row LM-head kernel streams it: 32-row groups of 1 KB
- * MFMA operand blocks), written once here: weight bytes include one more
- * V x d bf16 matrix.  Synchronous.  *out is set only on success.
+ * weights are 1.  The LM head is held once, in the order in which the few-row
+ * LM-head kernel streams it (32-row groups of 1 KB MFMA operand blocks, zero
+ * rows up to the next multiple of 32).  Synchronous.  *out is set only on success.
  * CORA_ERR_UNSUPPORTED when an activation matrix of max_batch x max_seq rows
  * (fp32 residual rows, bf16 FFN or attention-head rows, max_seq rounded up to
  * 64) would exceed 2 GB: the kernels address one with 32-bit byte offsets.
@@ -178,7 +177,7 @@ cora_status cora_forward_logits(cora_model *model, const int32_t *d_tokens, int3
  * and row reduction in chunks of up to 256 rows) under GLOBAL.  Eq. (1) is
  * computed inside the LM-head pass and no logits are written: when max_batch
  * times the rows scored per batch row (per chunk) is at most 64, the pass
- * streams the packed weight copy (per-128-entry partial max / first arg max /
+ * streams the weights (per-128-entry partial max / first arg max /
  * sum of exp), else each wavefront's logit columns are reduced in the tiled
  * GEMM's epilogue; the partials are merged in vocab order.  The top-1 is then
  * the same as cora_vocab_gate's on the logits cora_forward_logits writes for

@@ -8,7 +8,7 @@
 // Operands come in K panels of 32, so that every 1 KB load reads 1 KB of contiguous memory:
 //   A  [K / 32][M][32]: 16 rows of one panel are 1 KB
 //   W  (W_BLOCKS) 64 x 32 blocks, row-major inside, block (n / 64, k / 32) at
-//      ((n / 64) * K / 32 + k / 32) * 4 KB, N % 64 == 0; or (W_LM_HEAD) the LM head's packed
+//      ((n / 64) * K / 32 + k / 32) * 4 KB, N % 64 == 0; or (W_LM_HEAD) the LM head's
 //      layout (lm_head.hip), 1 KB blocks of 16 rows x 32 k in the MFMA operand's lane order,
 //      zero rows up to N's next multiple of 32.  These blocks go to LDS and come back as they
 //      are: a load that gathers their 16-byte chunks into 64-byte rows touches four times the
@@ -624,7 +624,7 @@ hipError_t launch_gemm(int epi, const GemmArgs& in, const GemmPlan& p, hipStream
   if (in.M == 0 || in.N == 0) return hipSuccess;
   // pairs of 32-wide slices; whole 64-row weight blocks; fp32 outputs in groups of 4 columns
   if (p.splits < 1 || in.K % (64 * p.splits) != 0) return hipErrorInvalidValue;
-  if (in.w_layout == W_BLOCKS && in.N % 64 != 0) return hipErrorInvalidValue;
+  if (in.w_layout != W_LM_HEAD && (in.w_layout != W_BLOCKS || in.N % 64 != 0)) return hipErrorInvalidValue;
   if ((epi == EPI_ADD_F32 || epi == EPI_PART_F32) && in.N % 4 != 0) return hipErrorInvalidValue;
   if (p.splits > 1 && epi != EPI_PART_F32) return hipErrorInvalidValue;
   GemmArgs a = in;

@@ -11,9 +11,12 @@ namespace cora {
 // 3: rows of q or k heads stored pair-interleaved within each head of hd rows (logical
 // j < hd/2 at 2j, logical j + hd/2 at 2j + 1), after row_offset.
 enum RowMap { ROW_IDENTITY = 0, ROW_GATE = 1, ROW_UP = 2, ROW_ROPE_PAIR = 3 };
+// Layout of a weight matrix: row-major (the embedding), 64 x 32 blocks (layer weights, ld % 32
+// == 0) or the LM head's operand blocks (ld % 64 == 0, lm_head_index)
+enum WLayout { W_ROW_MAJOR = 0, W_BLOCKS = 1, W_LM_HEAD = 2 };
 hipError_t launch_init_bf16(uint16_t* dst, uint64_t seed, uint64_t tensor_id, int64_t rows,
                             int64_t cols, int64_t ld, int row_map, int64_t row_offset, double std_dev,
-                            int head_dim, hipStream_t s, bool packed = false);
+                            int head_dim, hipStream_t s, WLayout layout);
 hipError_t launch_init_f32(float* dst, uint64_t seed, uint64_t tensor_id, int64_t n, double std_dev,
                            int pair_head_dim, hipStream_t s);
 // physical position of logical index j inside a head of hd pair-interleaved rows
@@ -58,9 +61,8 @@ hipError_t launch_scatter_rows(const int32_t* tokens, const int32_t* passes, con
                                int32_t* out_tokens, int32_t* out_passes, hipStream_t s);
 
 // ---- GEMM: C[M, N] = A[M, K] . W[N, K]^T, bf16 in, fp32 accumulate ---------------------
-// A in K panels [K / 32][M][32]; W in one of two layouts (see gemm.hip): 64 x 32 blocks
-// (layer weights, N % 64 == 0) or the LM head's packed layout
-enum GemmWLayout { W_BLOCKS = 0, W_LM_HEAD = 1 };
+// A in K panels [K / 32][M][32]; W in 64 x 32 blocks (N % 64 == 0) or in the LM head's layout
+// (see gemm.hip)
 enum GemmEpi {
   EPI_BF16 = 0, EPI_ADD_F32 = 1, EPI_SWIGLU = 2, EPI_QKV_ROPE = 3, EPI_PART_F32 = 4, EPI_TOP1 = 5
 };
@@ -83,7 +85,7 @@ struct QkvOut {
 struct GemmArgs {
   const uint16_t* A;
   const uint16_t* W;
-  int w_layout;
+  WLayout w_layout;  // W_BLOCKS or W_LM_HEAD
   int M, N, K;
   void* C; int64_t ldc;  // ldc unused by EPI_SWIGLU (panels of M rows) and EPI_QKV_ROPE
   const float* bias;   // EPI_BF16: per-column bias (or null)
@@ -121,7 +123,7 @@ hipError_t launch_qkv_finish(const float* part, int splits, int M, int N, const 
 // ---- LM head for few rows (M <= 64) ------------------------------------------------------
 struct LmHeadArgs {
   const uint16_t* A; int64_t lda;  // [M, K] normalised rows
-  const uint16_t* Wp;              // vocab projection [N, K] in the packed layout
+  const uint16_t* Wp;              // vocab projection [N, K] in its layout (lm_head_index)
   int M, N, K;
   float scale;                     // logit scale, applied before the bf16 rounding
   uint16_t* logits; int64_t ldc;   // logits mode: [M, N] bf16
@@ -132,9 +134,15 @@ struct LmHeadArgs {
 };
 constexpr int LM_HEAD_FUSED_MAX_ROWS = 64;
 int lm_head_parts(int N);
-// packed copy of the vocab projection (written once, read by launch_lm_head)
+// elements of the vocab projection in its layout (zero rows up to the next multiple of 32)
 size_t lm_head_packed_elems(int N, int K);
-hipError_t launch_pack_lm_head(const uint16_t* W, uint16_t* packed, int N, int K, hipStream_t s);
+// element (row, k) of the vocab projection [N, K], K % 64 == 0 (see lm_head.hip)
+__host__ __device__ inline int64_t lm_head_index(int64_t row, int64_t k, int64_t K) {
+  return (row >> 5) * 32 * K + (k >> 6) * 2048 + ((row >> 4) & 1) * 1024 + ((k >> 5) & 1) * 512 +
+         ((k >> 3) & 3) * 128 + (row & 15) * 8 + (k & 7);
+}
+// rows [row0, row0 + n) of the vocab projection, row-major
+hipError_t launch_unpack_lm_head(const uint16_t* W, uint16_t* rows, int row0, int n, int K, hipStream_t s);
 bool lm_head_supported(int M, int N, int K, int64_t lda);
 hipError_t launch_lm_head(const LmHeadArgs& a, bool top1, hipStream_t s);
 // rows are scored like launch_vocab_top1: row r of batch row b (n_rows per batch row) goes to

@@ -6,8 +6,8 @@
 // per weight byte), so the kernel is built for HBM, not for the matrix cores.  HBM delivers
 // ~6.8 TB/s to loads that cover 1 KB of contiguous memory per instruction, but only ~5.1
 // TB/s when an instruction covers 128 bytes of each of 8 rows 8 KB apart (the tile loads of
-// a row-major GEMM), so the weights are read from a packed copy made once at model
-// creation, laid out in the order this kernel consumes it:
+// a row-major GEMM), so the weights are held in the order this kernel consumes them
+// (lm_head_index, written so at model creation; the tiled GEMM reads the same):
 //   * wavefront G owns vocab rows 32 G .. 32 G + 31 (two 16-row MFMA blocks) over all of K;
 //     its 32 x K weights are one contiguous region of 1 KB blocks, block (stage st, block
 //     wb, step s) = rows 32 G + 16 wb + (0..15), k = 64 st + 32 s + (0..31), stored as the
@@ -47,29 +47,21 @@ int lm_head_parts(int N) { return (N + LMH_COLS - 1) / LMH_COLS; }
 __host__ __device__ inline int64_t packed_elems(int N, int K) { return (int64_t)((N + 31) / 32) * 32 * K; }
 size_t lm_head_packed_elems(int N, int K) { return (size_t)packed_elems(N, K); }
 
-// packed[G][st][wb][s][l][j] = W[32 G + 16 wb + l % 16][64 st + 32 s + 8 (l / 16) + j] (zero
-// past N): thread = one 16-byte chunk of the packed copy
-__global__ __launch_bounds__(256) void k_pack_lm_head(const uint16_t* __restrict__ W,
-                                                      uint16_t* __restrict__ P, int N, int K) {
+// thread = 8 consecutive elements of a row, one 16-byte piece in both layouts
+__global__ __launch_bounds__(256) void k_unpack_lm_head(const uint16_t* __restrict__ W,
+                                                        uint16_t* __restrict__ out, int row0, int n,
+                                                        int K) {
   const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t per_g = (int64_t)K * 4;  // chunks per 32-row group
-  if (c >= (int64_t)((N + 31) / 32) * per_g) return;
-  const int G = (int)(c / per_g);
-  const int rem = (int)(c - G * per_g);
-  const int blk = rem >> 6, l = rem & 63;
-  const int st = blk >> 2, wb = (blk >> 1) & 1, s = blk & 1;
-  const int row = 32 * G + 16 * wb + (l & 15), k = 64 * st + 32 * s + 8 * (l >> 4);
-  u32x4_t v = {0u, 0u, 0u, 0u};
-  if (row < N) v = *reinterpret_cast<const u32x4_t*>(W + (int64_t)row * K + k);
-  *reinterpret_cast<u32x4_t*>(P + c * 8) = v;
+  if (c >= (int64_t)n * (K / 8)) return;
+  const int64_t row = row0 + c / (K / 8), k = c % (K / 8) * 8;
+  *reinterpret_cast<u32x4_t*>(out + c * 8) =
+      *reinterpret_cast<const u32x4_t*>(W + lm_head_index(row, k, K));
 }
 
-hipError_t launch_pack_lm_head(const uint16_t* W, uint16_t* packed, int N, int K,
-                               hipStream_t s) {
-  if (N <= 0 || K % LMH_STAGE_K != 0) return hipErrorInvalidValue;
-  const int64_t chunks = packed_elems(N, K) / 8;
-  hipLaunchKernelGGL(k_pack_lm_head, dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, s, W,
-                     packed, N, K);
+hipError_t launch_unpack_lm_head(const uint16_t* W, uint16_t* rows, int row0, int n, int K, hipStream_t s) {
+  if (row0 < 0 || n <= 0 || K % LMH_STAGE_K != 0) return hipErrorInvalidValue;
+  const int64_t chunks = (int64_t)n * (K / 8);
+  hipLaunchKernelGGL(k_unpack_lm_head, dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, s, W, rows, row0, n, K);
   return hipGetLastError();
 }
 
@@ -85,7 +77,7 @@ __global__ __launch_bounds__(256) void k_lm_head(LmHeadArgs a) {
   const int r16 = lane & 15, q = lane >> 4;
   const int n_wave = blockIdx.x * LMH_COLS + wave * LMH_ROWS_PER_WAVE;
 
-  // buffer resources: activation rows past M read as zero; the packed weights are zero
+  // buffer resources: activation rows past M read as zero; the weights are zero
   // past N already
   const int64_t w_bytes = packed_elems(a.N, a.K) * 2;
   const int64_t a_bytes = (int64_t)a.M * a.lda * 2;
@@ -96,7 +88,7 @@ __global__ __launch_bounds__(256) void k_lm_head(LmHeadArgs a) {
   constexpr int OOB = 0x7fffffff;  // an offset past every buffer: zeros, no traffic
 
   // weights: this lane's 16 bytes of block (st, wb, s) of group G = n_wave / 32 (a group
-  // past the packed copy, in the last workgroup, reads zeros)
+  // past the matrix, in the last workgroup, reads zeros)
   const int64_t g_bytes = (int64_t)(n_wave / 32) * 32 * a.K * 2;
   const bool w_in = g_bytes < w_bytes;
   const int w_base = w_in ? (int)g_bytes + lane * 16 : 0;

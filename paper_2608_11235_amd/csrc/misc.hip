@@ -26,16 +26,18 @@ __device__ __forceinline__ float normal_from_counter(uint64_t key, uint64_t ctr,
   return (float)(std_dev * n);
 }
 
-// element (pr, c) of the physical matrix goes to pr * ld + c, or, packed (ld % 32 == 0), to
-// block (pr / 64, c / 32) of 64 x 32 (row-major inside), blocks ordered by row block then
-// column block
-__device__ __forceinline__ int64_t packed_index(int64_t pr, int64_t c, int64_t ld) {
+// element (pr, c) of the physical matrix goes to pr * ld + c (W_ROW_MAJOR), to lm_head_index
+// (W_LM_HEAD) or (W_BLOCKS) to block (pr / 64, c / 32) of 64 x 32 (row-major inside), blocks
+// ordered by row block then column block
+__device__ __forceinline__ int64_t weight_index(int64_t pr, int64_t c, int64_t ld, WLayout layout) {
+  if (layout == W_ROW_MAJOR) return pr * ld + c;
+  if (layout == W_LM_HEAD) return lm_head_index(pr, c, ld);
   return ((pr >> 6) * (ld >> 5) + (c >> 5)) * 2048 + (pr & 63) * 32 + (c & 31);
 }
 
 __global__ void k_init_bf16(uint16_t* __restrict__ dst, uint64_t key, uint64_t base, int64_t rows,
                             int64_t cols, int64_t ld, int row_map, int64_t row_offset,
-                            double std_dev, int hd, int packed) {
+                            double std_dev, int hd, WLayout layout) {
   for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
     int64_t pr;
     if (row_map == ROW_GATE) pr = (r >> 4) * 32 + (r & 15);
@@ -44,7 +46,7 @@ __global__ void k_init_bf16(uint16_t* __restrict__ dst, uint64_t key, uint64_t b
     else pr = row_offset + r;
     for (int64_t c = threadIdx.x; c < cols; c += blockDim.x) {
       const uint64_t ctr = base | (uint64_t)(r * cols + c);
-      dst[packed ? packed_index(pr, c, ld) : pr * ld + c] =
+      dst[weight_index(pr, c, ld, layout)] =
           (uint16_t)f32_to_bf16_bits(normal_from_counter(key, ctr, std_dev));
     }
   }
@@ -78,12 +80,13 @@ static uint64_t host_mix64(uint64_t z) {
 
 hipError_t launch_init_bf16(uint16_t* dst, uint64_t seed, uint64_t tensor_id, int64_t rows,
                             int64_t cols, int64_t ld, int row_map, int64_t row_offset, double std_dev,
-                            int head_dim, hipStream_t s, bool packed) {
-  if (packed && ld % 32 != 0) return hipErrorInvalidValue;
+                            int head_dim, hipStream_t s, WLayout layout) {
+  if ((layout == W_BLOCKS && ld % 32 != 0) || (layout == W_LM_HEAD && ld % 64 != 0))
+    return hipErrorInvalidValue;
   const int grid = (int)(rows < 16384 ? rows : 16384);
   hipLaunchKernelGGL(k_init_bf16, dim3(grid), dim3(256), 0, s, dst, host_mix64(seed),
                      tensor_id << 40, rows, cols, ld, row_map, row_offset, std_dev, head_dim,
-                     packed ? 1 : 0);
+                     layout);
   return hipGetLastError();
 }
 

@@ -68,6 +68,20 @@ def test_device_bytes():
     assert 0 < ws1 < ws2
 
 
+def test_lm_head_is_held_once():
+    """Without layers the weights are the embedding and the LM head, each once (the LM head with
+    rows up to the next multiple of 32), 4-byte norm weights, and the alignment of three arrays."""
+    require_gpu()
+    import dataclasses
+    from paper_2608_11235_amd import Model
+    spec = dataclasses.replace(SPEC, n_layers=0, d_model=128, vocab=20001)
+    log_case("device bytes: one LM head")
+    with Model(spec, seed=0, max_batch=1, max_seq=8) as m:
+        w, _ = m.device_bytes()
+    d, V = spec.d_model, spec.vocab
+    assert 2 * d * (V + 20032) <= w <= 2 * d * (V + 20032) + 4 * d + 3 * 4096
+
+
 def test_binding_refuses_misread_tensors():
     require_gpu()
     import torch

@@ -44,6 +44,20 @@ def test_weights_bit_exact(spec):
             assert (got == want).all(), f"tensor {tid}: {(got != want).sum()} mismatches"
 
 
+@pytest.mark.parametrize("vocab", [2, 32, 33, 20001])
+def test_lm_head_bit_exact(vocab):
+    """The LM head comes back row-major from its operand layout; 20001 rows of 1088 columns take
+    more than one piece."""
+    require_gpu()
+    from paper_2608_11235_amd import Model
+    spec = replace(si.TINY, n_layers=0, d_model=1088, vocab=vocab, mask_id=1)
+    log_case(f"LM head weights V={vocab}")
+    with Model(spec, seed=3, max_batch=1, max_seq=8) as m:
+        got = m.copy_tensor(si.TENSOR_LM_HEAD, vocab * spec.d_model)
+    want = si.gen_tensor(3, si.TENSOR_LM_HEAD, (vocab, spec.d_model), spec.init_std, as_bits=True)
+    assert (got == want.reshape(-1)).all()
+
+
 def _check_logits(spec, B, L, row_begin, n_rows, seed=0, tag=""):
     from paper_2608_11235_amd import Model
     log_case(f"forward {spec.name} B={B} L={L} rows=[{row_begin},{row_begin + n_rows}) {tag}")
