@@ -83,7 +83,7 @@ __device__ __forceinline__ void wait_vm() {
 __device__ __forceinline__ void load_lds(uint32_t lds_off, int voff, u32x4_t rs, int soff) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds_off),
                "v"(voff), "s"(rs), "s"(soff)
-               : "memory");
+               : "memory", "m0");
 }
 
 __device__ __forceinline__ u32x4_t buffer_rsrc(const void* p, int64_t bytes) {
