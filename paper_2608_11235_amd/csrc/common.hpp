@@ -51,6 +51,15 @@ __device__ __forceinline__ float warp_sum(float v) {
   return v;
 }
 
+// Where the lanes of one wavefront exchange data through LDS of its own: what they wrote before
+// is what any of them reads after, and the compiler moves no access across.  The LDS takes a
+// wavefront's accesses in order, so this is no instruction.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---- softmax statistics of a row (Eq. 1) ---------------------------------------------------
 // Partial (max, sum of exp(l - max), lowest index holding the max) over a set of logits;
 // an empty set is (-inf, 0, INT_MAX).

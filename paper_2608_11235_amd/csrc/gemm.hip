@@ -364,6 +364,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, OCC) void k_gemm(GemmArgs g)
 #pragma unroll
           for (int e = 0; e < 4; ++e) scr[(4 * fc + e) * SPV + at] = (uint16_t)f32_to_bf16_bits(acc[i][j][e]);
         }
+        wave_lds_sync();
         const uint16_t* src = scr + (lane >> 2) * SPV;
         const int64_t dim = (int64_t)head * hd + d0 + (lane >> 2), seq = (int64_t)o.n_kv_heads * hd;
         if (two) {
@@ -384,6 +385,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, OCC) void k_gemm(GemmArgs g)
             o.vt[(bb * seq + dim) * o.Ls + m - bb * o.L] = src[r];
           }
         }
+        wave_lds_sync();  // the next block is staged in the same place
       }
     }
   } else if constexpr (EPI == EPI_TOP1) {
