@@ -32,7 +32,7 @@ RAGGED = si.ModelSpec("lmhead-ragged", 0, 192, 3, 3, 64, 64, 5000, 4321, False, 
 LLADA_HEAD = si.ModelSpec("lmhead-llada", 0, 4096, 32, 32, 128, 128, 126464, 126336, False,
                           1e-5, 5e5, 1.0)
 # 0 layers, vocab 24100 at 512 scored rows: the planner takes the 256 x 192 tile, whose last
-# tile column holds 100 valid columns (one wavefront column range entirely past the vocab)
+# tile column holds 100 valid columns (4 of them in its second wavefront column range)
 WIDE = si.ModelSpec("lmhead-wide", 0, 256, 4, 4, 64, 64, 24100, 24007, False, 1e-5, 1e4, 2.0)
 BLK = 32
 
@@ -52,8 +52,8 @@ def _host_scores(logits, mask_id):
                                         (WIDE, 2, 256)],
                          ids=lambda v: getattr(v, "name", str(v)))
 def test_fused_scores_match_own_logits(spec, B, blk):
-    """B x blk = 32, 64: packed-weight stream; 96 (256 x 128 tiles), 512 (256 x 192 tiles):
-    the tiled GEMM's top-1 epilogue."""
+    """B x blk = 32, 64: packed-weight stream; 96 (32 x 64 and 64 x 64 tiles), 512 (256 x 192
+    tiles): the tiled GEMM's top-1 epilogue."""
     require_gpu()
     from paper_2608_11235_amd import DecodeState, Gate, Model, Sched
     P, G = 32, max(64, blk)
