@@ -142,7 +142,7 @@ static cora_status validate_cfg(const cora_model_cfg& c) {
   if (c.d_model > RESIDUAL_NORM_MAX_D)
     return fail(CORA_ERR_UNSUPPORTED, "d_model must not exceed 8192");
   {
-    // the GEMMs address every layer matrix with 32-bit byte offsets
+    // a layer matrix stays within what a 32-bit byte offset reaches
     const int64_t hq = (int64_t)c.n_heads * c.head_dim, hkv = (int64_t)c.n_kv_heads * c.head_dim;
     const int64_t fp = ((int64_t)c.ffn_dim + 63) / 64 * 64, d = c.d_model;
     const int64_t largest = std::max({(hq + 2 * hkv) * d, d * hq, 2 * fp * d, d * fp});
