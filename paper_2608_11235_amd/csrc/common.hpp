@@ -77,7 +77,8 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // exp(v - m) of bf16 logits v and their finite maximum m, summed over some v: one fma per logit,
 // 2^(v k + o).  Below |m| = 2^14: k = log2 e, o = -m k rounded; the rounding scales every term
 // alike, by 2^(m k + o), which `sum` takes back (to first order: what is left is at most 2.3e-7,
-// and 1e-9 below |m| = 2^10).  From 2^14 on that error would grow with |m| (inf or 0 at 4e9,
+// and 1e-9 below |m| = 2^10; the rms error of confidences of 126464 logits N(0, 6^2) against 64
+// bits is 9e-8, 4e-7 without).  From 2^14 on that error would grow with |m| (inf or 0 at 4e9,
 // inf - inf at bf16's lowest number, a usual fill of banned tokens), but two different bf16
 // numbers are 64 or more apart, so that a term is 1 where v == m and nothing a sum can notice
 // elsewhere: k = 1, o = -m, exact.  (v - m) * log2 e for every m is one operation more a logit:
