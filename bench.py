@@ -36,8 +36,8 @@ TIME_EVERY = 4              # gate/up event timing on every 4th timed pass
 # file and the shared device headers.
 SHARED_SOURCES = ("paper_2608_11235_amd/csrc/common.hpp", "paper_2608_11235_amd/csrc/internal.hpp")
 COUNTER_TRAFFIC = {
-    "gate_up": ("paper_2608_11235_amd/csrc/gemm.hip", "e6476cbe77e4bdc7", 247638118),
-    "vocab_gate": ("paper_2608_11235_amd/csrc/vocab_gate.hip", "8158577e35d7c498", 1036529255),
+    "gate_up": ("paper_2608_11235_amd/csrc/gemm.hip", "032c1ccaf751ffef", 247659110),
+    "vocab_gate": ("paper_2608_11235_amd/csrc/vocab_gate.hip", "f327780c6af0bdcb", 1036531302),
 }
 
 
